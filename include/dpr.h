@@ -382,8 +382,9 @@ int dpr_consistency_filter(int64_t n, int32_t sh_degree, const float *xyz, const
  * coefficients of its k nearest S1 points.
  * Squared distances in float32, each operation rounded once:
  * d2(x, y) = ((x0 - y0)^2 + (x1 - y1)^2) + (x2 - y2)^2; a nearest neighbour is
- * the point of smallest d2, ties to the lower index.  Brute force: the work
- * grows as n1 * n2 (meant for clouds of one frame, up to about 10^6 points).
+ * the point of smallest d2, ties to the lower index.  dpr_chamfer and
+ * dpr_topk_sh_ws search through a grid of cells (brute force for small clouds);
+ * dpr_topk_sh, which has no workspace, by brute force: its work grows as n1 * n2.
  * ------------------------------------------------------------------------- */
 
 /* Bytes of the device workspace of dpr_chamfer (0 on bad sizes). */
@@ -405,6 +406,14 @@ int dpr_chamfer(int64_t n1, const float *s1, int64_t n2, const float *s2, double
  * int32, -1 past k; NULL to skip).  Asynchronous on `stream`. */
 int dpr_topk_sh(int64_t n1, const float *s1, const float *sh1, int64_t n2, const float *s2, int32_t sh_degree,
                 int32_t K, float *out_sh2, int32_t *idx, void *stream);
+
+/* dpr_topk_sh with a device workspace (16-byte aligned) of
+ * dpr_topk_sh_ws_bytes bytes (0 on bad sizes), needed until the work on
+ * `stream` has run: the same results through a grid of cells.
+ * DPR_ERR_WORKSPACE if it is NULL or smaller.  Asynchronous on `stream`. */
+size_t dpr_topk_sh_ws_bytes(int64_t n1, int64_t n2, int32_t K);
+int dpr_topk_sh_ws(int64_t n1, const float *s1, const float *sh1, int64_t n2, const float *s2, int32_t sh_degree,
+                   int32_t K, float *out_sh2, int32_t *idx, void *ws, size_t ws_bytes, void *stream);
 
 /* One Adam step (Kingma and Ba, ICLR 2015) on n values in float32, in place
  * on p, m, v (device), step t >= 1 with bias correction:

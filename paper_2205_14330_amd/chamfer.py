@@ -55,8 +55,11 @@ def topk_sh(s1: torch.Tensor, sh1: torch.Tensor, s2: torch.Tensor, K: int, with_
     n1, n2 = int(s1.shape[0]), int(s2.shape[0])
     out = torch.empty((n2,) + tuple(sh1.shape[1:]), dtype=torch.float32, device=s1.device)
     idx = torch.empty((n2, K), dtype=torch.int32, device=s1.device) if with_index else None
-    check(lib.dpr_topk_sh(n1, s1.data_ptr(), sh1.data_ptr(), n2, s2.data_ptr(), deg, int(K), out.data_ptr(),
-                          idx.data_ptr() if idx is not None else None, _stream_handle(stream)))
+    # 0 (bad sizes): the call itself says which
+    ws = torch.empty(max(int(lib.dpr_topk_sh_ws_bytes(n1, n2, int(K))), 1), dtype=torch.uint8, device=s1.device)
+    check(lib.dpr_topk_sh_ws(n1, s1.data_ptr(), sh1.data_ptr(), n2, s2.data_ptr(), deg, int(K), out.data_ptr(),
+                             idx.data_ptr() if idx is not None else None, ws.data_ptr(), int(ws.numel()),
+                             _stream_handle(stream)))
     return (out, idx) if with_index else out
 
 

@@ -4,150 +4,142 @@
 // them, and the transfer to each S2 point of the mean SH coefficients of its
 // k nearest S1 points.
 //
-// Nearest neighbours by brute force over LDS tiles: a block takes 256 threads
-// x 2 queries against one 4096-point range of the other cloud (so that a frame
-// of some 10^4 points still fills the GPU), and folds its result into a
-// 64-bit key per query with one atomic minimum: key = (d2 bits << 32) | index,
-// which orders by (d2, index) because d2 >= 0 (ties go to the lower index,
-// whatever the order in which the blocks finish).  Distances in float32 with
-// each operation rounded: ((dx dx + dy dy) + dz dz).  Sums of Eq. (9) in FP64
-// (block partials, then one block in a fixed order); the gradient term that
-// collects the S1 points whose nearest is y_j uses FP64 atomics.
+// Nearest neighbours by brute force here (nn_brute.h); larger clouds are
+// searched through a grid (chamfer_grid.hip) with the same results.  Four
+// launches: both directions' keys cleared, searched, collected (Eq. (9)'s FP64
+// block sums, and per S2 point the FP64 sum of the S1 points whose nearest it
+// is), and the gradient with the final sum.  For 2000 points that is 25 us,
+// where twelve launches and 4096-point ranges took 118.
 // Top-k: one thread per query keeps its k best keys in registers (sorted)
 // while all of S1 streams through LDS; SH means in FP64 in neighbour order.
 #include <cmath>
 
 #include "dpr_internal.h"
+#include "nn_brute.h"
 
 #pragma clang fp contract(off)
 
 namespace dpr {
 
-constexpr int kNnThreads = 256;
-constexpr int kNnQueries = 2;                          // queries per thread
-constexpr int kNnTile = 1024;                          // candidate points per LDS tile
-constexpr int kNnRange = 4096;                         // candidate points per block
-
-__device__ __forceinline__ float d2f(float ax, float ay, float az, float bx, float by, float bz) {
-    const float a = ax - bx, b = ay - by, c = az - bz;
-    float s = a * a;
-    s = s + b * b;
-    return s + c * c;
+__global__ __launch_bounds__(kNnThreads) void k_nn(NnJob a, NnJob b) {
+    if (blockIdx.x < a.qblocks) nn_brute(a, blockIdx.x, blockIdx.y);
+    else nn_brute(b, blockIdx.x - a.qblocks, blockIdx.y);
 }
 
-// key[i] = min over this block's candidate range of (d2(q_i, c_j) bits << 32 | j)
-__global__ __launch_bounds__(kNnThreads) void k_nn(const float *q, uint32_t nq, const float *c, uint32_t nc,
-                                                   unsigned long long *key) {
-    __shared__ float s_x[kNnTile], s_y[kNnTile], s_z[kNnTile];
-    const uint32_t q0 = blockIdx.x * (kNnThreads * kNnQueries) + threadIdx.x;
-    const uint32_t cbeg = blockIdx.y * (uint32_t)kNnRange, cend = min(cbeg + (uint32_t)kNnRange, nc);
-    float qx[kNnQueries], qy[kNnQueries], qz[kNnQueries], best[kNnQueries];
-    uint32_t bj[kNnQueries];
-#pragma unroll
-    for (int k = 0; k < kNnQueries; ++k) {
-        const uint32_t i = q0 + k * kNnThreads;
-        const uint32_t ii = i < nq ? i : 0;
-        qx[k] = q[3 * (size_t)ii]; qy[k] = q[3 * (size_t)ii + 1]; qz[k] = q[3 * (size_t)ii + 2];
-        best[k] = INFINITY;
-        bj[k] = 0xFFFFFFFFu;
-    }
-    for (uint32_t t0 = cbeg; t0 < cend; t0 += kNnTile) {
-        const uint32_t tn = min((uint32_t)kNnTile, cend - t0);
-        __syncthreads();
-        for (uint32_t t = threadIdx.x; t < tn; t += kNnThreads) {
-            s_x[t] = c[3 * (size_t)(t0 + t)];
-            s_y[t] = c[3 * (size_t)(t0 + t) + 1];
-            s_z[t] = c[3 * (size_t)(t0 + t) + 2];
-        }
-        __syncthreads();
-        for (uint32_t t = 0; t < tn; ++t) {
-            const float cx = s_x[t], cy = s_y[t], cz = s_z[t];
-#pragma unroll
-            for (int k = 0; k < kNnQueries; ++k) {
-                const float d = d2f(qx[k], qy[k], qz[k], cx, cy, cz);
-                if (d < best[k]) {          // scanning in index order: the first minimum is the lowest index
-                    best[k] = d;
-                    bj[k] = t0 + t;
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < kNnQueries; ++k) {
-        const uint32_t i = q0 + k * kNnThreads;
-        if (i < nq && bj[k] != 0xFFFFFFFFu)
-            atomicMin(key + i, ((unsigned long long)__float_as_uint(best[k]) << 32) | bj[k]);
-    }
-}
-
-__global__ void k_fill_u64(unsigned long long *p, unsigned long long v, uint32_t n) {
+// key12, key21 = ~0; acc, cnt = 0 (acc may be null)
+__global__ void k_chamfer_clear(unsigned long long *key12, uint32_t n1, unsigned long long *key21, uint32_t n2,
+                                double *acc, uint32_t *cnt) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-static hipError_t nearest(const float *q, uint32_t nq, const float *c, uint32_t nc, unsigned long long *key,
-                          hipStream_t st) {
-    hipLaunchKernelGGL(k_fill_u64, dim3((nq + 255) / 256), dim3(256), 0, st, key, ~0ull, nq);
-    const dim3 grid((nq + kNnThreads * kNnQueries - 1) / (kNnThreads * kNnQueries), (nc + kNnRange - 1) / kNnRange);
-    hipLaunchKernelGGL(k_nn, grid, dim3(kNnThreads), 0, st, q, nq, c, nc, key);
-    return hipGetLastError();
-}
-
-// per S2 point j: acc[j] = sum of the S1 points whose nearest is j (FP64), cnt[j] their number
-__global__ void k_collect(const unsigned long long *key12, uint32_t n1, const float *s1, double *acc, uint32_t *cnt) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n1) return;
-    const uint32_t j = (uint32_t)(key12[i] & 0xFFFFFFFFull);
+    if (i < n1) key12[i] = ~0ull;
+    if (i >= n2) return;
+    key21[i] = ~0ull;
+    if (!acc) return;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) atomicAdd(acc + 3 * (size_t)j + a, (double)s1[3 * (size_t)i + a]);
-    atomicAdd(cnt + j, 1u);
-}
-
-// grad2[j] = 2/n2 (y_j - nn(y_j)) + 2/n1 (cnt_j y_j - acc_j), FP64 then rounded
-__global__ void k_grad(const unsigned long long *key21, uint32_t n2, const float *s2, const float *s1, uint32_t n1,
-                       const double *acc, const uint32_t *cnt, float *grad2, int32_t *nn21) {
-    const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n2) return;
-    const uint32_t k = (uint32_t)(key21[j] & 0xFFFFFFFFull);
-    if (nn21) nn21[j] = (int32_t)k;
-    if (!grad2) return;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const double y = (double)s2[3 * (size_t)j + a];
-        const double g = 2.0 / (double)n2 * (y - (double)s1[3 * (size_t)k + a]) +
-                         2.0 / (double)n1 * ((double)cnt[j] * y - acc[3 * (size_t)j + a]);
-        grad2[3 * (size_t)j + a] = (float)g;
-    }
-}
-
-__global__ void k_nn_index(const unsigned long long *key, uint32_t n, int32_t *nn) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) nn[i] = (int32_t)(uint32_t)(key[i] & 0xFFFFFFFFull);
+    for (int a = 0; a < 3; ++a) acc[3 * (size_t)i + a] = 0.0;
+    cnt[i] = 0u;
 }
 
 constexpr int kSumThreads = 256;
 
-// part[b] = FP64 sum of the d2 of keys [b 256 .. ), in index order within the block
-__global__ __launch_bounds__(kSumThreads) void k_sum_d2(const unsigned long long *key, uint32_t n, double *part) {
+// Both directions' keys, blocks [0, blocks1) of S1 then those of S2:
+//   nn = the nearest's index; part[b] = FP64 sum of the block's d2, in a fixed
+//   order; per S2 point j: acc[j] = sum of the S1 points whose nearest is j
+//   (FP64), cnt[j] their number.  Null outputs are skipped.
+struct ChamferSums {
+    const unsigned long long *key12, *key21;
+    uint32_t n1, n2, blocks1;
+    const float *s1;
+    int32_t *nn12, *nn21;
+    double *part1, *part2, *acc;
+    uint32_t *cnt;
+};
+
+__global__ __launch_bounds__(kSumThreads) void k_collect(ChamferSums c) {
     __shared__ double s[kSumThreads];
-    const uint32_t i = blockIdx.x * kSumThreads + threadIdx.x;
-    s[threadIdx.x] = i < n ? (double)__uint_as_float((uint32_t)(key[i] >> 32)) : 0.0;
+    const bool first = blockIdx.x < c.blocks1;
+    const uint32_t blk = first ? blockIdx.x : blockIdx.x - c.blocks1;
+    const uint32_t i = blk * kSumThreads + threadIdx.x, n = first ? c.n1 : c.n2;
+    const unsigned long long key = i < n ? (first ? c.key12 : c.key21)[i] : 0ull;
+    if (i < n) {
+        const uint32_t j = (uint32_t)(key & 0xFFFFFFFFull);
+        int32_t *const nn = first ? c.nn12 : c.nn21;
+        if (nn) nn[i] = (int32_t)j;
+        if (first && c.acc && j < c.n2) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) atomicAdd(c.acc + 3 * (size_t)j + a, (double)c.s1[3 * (size_t)i + a]);
+            atomicAdd(c.cnt + j, 1u);
+        }
+    }
+    double *const part = first ? c.part1 : c.part2;
+    if (!part) return;
+    s[threadIdx.x] = i < n ? (double)__uint_as_float((uint32_t)(key >> 32)) : 0.0;
     __syncthreads();
     for (int w = kSumThreads / 2; w >= 1; w >>= 1) {
         if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = s[0];
+    if (threadIdx.x == 0) part[blk] = s[0];
 }
 
-// cd = (sum part1) / n1 + (sum part2) / n2, each summed in block order by one thread
-__global__ void k_cd(const double *part1, uint32_t nb1, uint32_t n1, const double *part2, uint32_t nb2, uint32_t n2,
-                     double *cd) {
-    if (threadIdx.x != 0) return;
-    double a = 0.0, b = 0.0;
-    for (uint32_t k = 0; k < nb1; ++k) a += part1[k];
-    for (uint32_t k = 0; k < nb2; ++k) b += part2[k];
-    *cd = a / (double)n1 + b / (double)n2;
+// The sum of n values by the whole block: thread t adds t, t + 256, ..., then a tree (a fixed order).
+__device__ __forceinline__ double block_sum(const double *v, uint32_t n, double *s) {
+    double a = 0.0;
+    for (uint32_t k = threadIdx.x; k < n; k += kSumThreads) a += v[k];
+    s[threadIdx.x] = a;
+    __syncthreads();
+    for (int w = kSumThreads / 2; w >= 1; w >>= 1) {
+        if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
+        __syncthreads();
+    }
+    const double r = s[0];
+    __syncthreads();
+    return r;
+}
+
+// grad2[j] = 2/n2 (y_j - nn(y_j)) + 2/n1 (cnt_j y_j - acc_j), FP64 then rounded;
+// the last block (if cd): cd = (sum part1) / n1 + (sum part2) / n2
+__global__ __launch_bounds__(kSumThreads) void k_grad(ChamferSums c, const float *s2, float *grad2, double *cd) {
+    __shared__ double s[kSumThreads];
+    if (cd && blockIdx.x == gridDim.x - 1) {
+        const double a = block_sum(c.part1, c.blocks1, s);
+        const double b = block_sum(c.part2, (c.n2 + kSumThreads - 1) / kSumThreads, s);
+        if (threadIdx.x == 0) *cd = a / (double)c.n1 + b / (double)c.n2;
+        return;
+    }
+    const uint32_t j = blockIdx.x * kSumThreads + threadIdx.x;
+    if (j >= c.n2) return;
+    const uint32_t k = (uint32_t)(c.key21[j] & 0xFFFFFFFFull);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double y = (double)s2[3 * (size_t)j + a];
+        const double x = k < c.n1 ? (double)c.s1[3 * (size_t)k + a] : (double)NAN;    // no neighbour: a NaN point
+        const double g = 2.0 / (double)c.n2 * (y - x) +
+                         2.0 / (double)c.n1 * ((double)c.cnt[j] * y - c.acc[3 * (size_t)j + a]);
+        grad2[3 * (size_t)j + a] = (float)g;
+    }
+}
+
+hipError_t launch_chamfer_finish(uint32_t n1, const float *s1, uint32_t n2, const float *s2, double *cd, float *grad2,
+                                 int32_t *nn12, int32_t *nn21, uint8_t *ws, hipStream_t st) {
+    const ChamferLayout L = chamfer_layout(n1, n2);
+    const uint32_t nb1 = (n1 + kSumThreads - 1) / kSumThreads, nb2 = (n2 + kSumThreads - 1) / kSumThreads;
+    ChamferSums c;
+    c.key12 = reinterpret_cast<unsigned long long *>(ws + L.key12);
+    c.key21 = reinterpret_cast<unsigned long long *>(ws + L.key21);
+    c.n1 = n1;
+    c.n2 = n2;
+    c.blocks1 = nb1;
+    c.s1 = s1;
+    c.nn12 = nn12;
+    c.nn21 = nn21;
+    c.part1 = cd ? reinterpret_cast<double *>(ws + L.part1) : nullptr;
+    c.part2 = cd ? reinterpret_cast<double *>(ws + L.part2) : nullptr;
+    c.acc = grad2 ? reinterpret_cast<double *>(ws + L.acc) : nullptr;
+    c.cnt = reinterpret_cast<uint32_t *>(ws + L.cnt);
+    hipLaunchKernelGGL(k_collect, dim3(nb1 + nb2), dim3(kSumThreads), 0, st, c);
+    const uint32_t gb = (grad2 ? nb2 : 0u) + (cd ? 1u : 0u);
+    if (gb) hipLaunchKernelGGL(k_grad, dim3(gb), dim3(kSumThreads), 0, st, c, s2, grad2, cd);
+    return hipGetLastError();
 }
 
 ChamferLayout chamfer_layout(uint64_t n1, uint64_t n2) {
@@ -174,30 +166,12 @@ hipError_t launch_chamfer(uint32_t n1, const float *s1, uint32_t n2, const float
     auto *key12 = reinterpret_cast<unsigned long long *>(ws + L.key12);
     auto *key21 = reinterpret_cast<unsigned long long *>(ws + L.key21);
     double *acc = reinterpret_cast<double *>(ws + L.acc);
-    uint32_t *cnt = reinterpret_cast<uint32_t *>(ws + L.cnt);
-    double *part1 = reinterpret_cast<double *>(ws + L.part1), *part2 = reinterpret_cast<double *>(ws + L.part2);
-    hipError_t e = nearest(s1, n1, s2, n2, key12, st);
-    if (e != hipSuccess) return e;
-    e = nearest(s2, n2, s1, n1, key21, st);
-    if (e != hipSuccess) return e;
-    const uint32_t nb1 = (n1 + kSumThreads - 1) / kSumThreads, nb2 = (n2 + kSumThreads - 1) / kSumThreads;
-    if (cd) {
-        hipLaunchKernelGGL(k_sum_d2, dim3(nb1), dim3(kSumThreads), 0, st, key12, n1, part1);
-        hipLaunchKernelGGL(k_sum_d2, dim3(nb2), dim3(kSumThreads), 0, st, key21, n2, part2);
-        hipLaunchKernelGGL(k_cd, dim3(1), dim3(64), 0, st, part1, nb1, n1, part2, nb2, n2, cd);
-    }
-    if (nn12) hipLaunchKernelGGL(k_nn_index, dim3((n1 + 255) / 256), dim3(256), 0, st, key12, n1, nn12);
-    if (grad2) {
-        e = launch_fill_u32(reinterpret_cast<uint32_t *>(acc), 0u, 6ull * n2, st);
-        if (e != hipSuccess) return e;
-        e = launch_fill_u32(cnt, 0u, n2, st);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_collect, dim3((n1 + 255) / 256), dim3(256), 0, st, key12, n1, s1, acc, cnt);
-    }
-    if (grad2 || nn21)
-        hipLaunchKernelGGL(k_grad, dim3((n2 + 255) / 256), dim3(256), 0, st, key21, n2, s2, s1, n1, acc, cnt, grad2,
-                           nn21);
-    return hipGetLastError();
+    const uint32_t most = n1 > n2 ? n1 : n2;
+    hipLaunchKernelGGL(k_chamfer_clear, dim3((most + 255) / 256), dim3(256), 0, st, key12, n1, key21, n2,
+                       grad2 ? acc : nullptr, reinterpret_cast<uint32_t *>(ws + L.cnt));
+    const NnJob a = nn_job(s1, n1, s2, n2, key12), b = nn_job(s2, n2, s1, n1, key21);
+    hipLaunchKernelGGL(k_nn, dim3(a.qblocks + b.qblocks, a.ranges > b.ranges ? a.ranges : b.ranges), dim3(kNnThreads), 0, st, a, b);
+    return launch_chamfer_finish(n1, s1, n2, s2, cd, grad2, nn12, nn21, ws, st);
 }
 
 // Top-k: a group of kTopkLanes consecutive lanes per query y of S2.  Lane s of

@@ -305,8 +305,8 @@ hipError_t launch_radix_sort(uint32_t n, int bits, uint32_t *keys, uint32_t *val
 
 // Hybrid coarse-to-fine update (hybrid.hip).
 constexpr int kKnnMax = 32;               // largest K
-constexpr uint32_t kKnnMaxGrid = 128;     // neighbour grid cells per axis, at most
 constexpr uint32_t kHyBoxBlocks = 256;    // blocks of the bounding-box reduction
+constexpr uint32_t kKnnMaxGrid = 128;     // neighbour grid cells per axis, at most
 struct HyScratch {
     uint32_t *keys, *vals, *keys_alt, *vals_alt;   // [n] each
     uint32_t *hist;                               // radix_hist_words(n) + 1
@@ -370,12 +370,28 @@ hipError_t launch_hull(const HullJob &job, uint8_t *ws, uint64_t *kept_host, hip
 
 // Video warm start: Chamfer distance, top-k SH transfer, Adam (chamfer.hip).
 constexpr int kTopkMax = 32;
+// n1 n2 from which the grid is searched: its seven to nine launches cost about
+// 40 us however small the clouds.  Eq. (9) of 6000 and 8000 points takes 34 and
+// 42 us by brute force (12000: 82, against 43); the 4 nearest 35 us for 500
+// points and 53 for 1000.
+constexpr double kChamferGridPairs = 6.4e7, kTopkGridPairs = 5.0e5;
 struct ChamferLayout {
     uint64_t key12, key21, acc, cnt, part1, part2, bytes;
 };
 ChamferLayout chamfer_layout(uint64_t n1, uint64_t n2);
 hipError_t launch_chamfer(uint32_t n1, const float *s1, uint32_t n2, const float *s2, double *cd, float *grad2,
                           int32_t *nn12, int32_t *nn21, uint8_t *ws, hipStream_t st);
+// From both directions' keys (in ws) to Eq. (9), its gradient and the indices.
+hipError_t launch_chamfer_finish(uint32_t n1, const float *s1, uint32_t n2, const float *s2, double *cd, float *grad2,
+                                 int32_t *nn12, int32_t *nn21, uint8_t *ws, hipStream_t st);
+// The same results through a grid of cells (chamfer_grid.hip); ws: chamfer_grid_bytes,
+// topk_grid_bytes.
+uint64_t chamfer_grid_bytes(uint64_t n1, uint64_t n2);
+hipError_t launch_chamfer_grid(uint32_t n1, const float *s1, uint32_t n2, const float *s2, double *cd, float *grad2,
+                               int32_t *nn12, int32_t *nn21, uint8_t *ws, hipStream_t st);
+uint64_t topk_grid_bytes(uint64_t n1, uint64_t n2, int K);
+hipError_t launch_topk_grid(uint32_t n1, const float *s1, const float *sh1, uint32_t n2, const float *s2, int k3,
+                            int K, float *out_sh, int32_t *idx, uint8_t *ws, hipStream_t st);
 hipError_t launch_topk_sh(uint32_t n1, const float *s1, const float *sh1, uint32_t n2, const float *s2, int k3, int K,
                           float *out_sh, int32_t *idx, hipStream_t st);
 hipError_t launch_adam(uint32_t n, float *p, const float *g, float *m, float *v, int t, float lr, float b1, float b2,
