@@ -306,19 +306,17 @@ hipError_t launch_radix_sort(uint32_t n, int bits, uint32_t *keys, uint32_t *val
 // Hybrid coarse-to-fine update (hybrid.hip).
 constexpr int kKnnMax = 32;               // largest K
 constexpr uint32_t kHyBoxBlocks = 256;    // blocks of the bounding-box reduction
-constexpr uint32_t kKnnMaxGrid = 128;     // neighbour grid cells per axis, at most
 struct HyScratch {
     uint32_t *keys, *vals, *keys_alt, *vals_alt;   // [n] each
     uint32_t *hist;                               // radix_hist_words(n) + 1
     uint64_t *part;                               // scan_partials(max(n + 1, hist words)) + 1
     uint64_t *total64;
     uint32_t *flags, *seg, *starts;               // [n + 2] each
-    uint32_t *cell_start;                         // [cells of the neighbour grid + 1]
+    uint32_t *cell_start;                         // the neighbour grid (grid_bytes of nn_grid.h; 16-byte aligned)
     float *box_part, *box;                        // [6 kHyBoxBlocks], [6]
     int32_t *idx;                                 // [n K]
     float *d2;                                    // [n K]
 };
-uint32_t knn_grid_size(uint64_t m);
 // Bytes of each HyScratch array for up to n points and K neighbours.
 struct HyScratchBytes {
     uint64_t keys, vals, keys_alt, vals_alt, hist, part, total64, flags, seg, starts, cell_start, box_part, box, idx,

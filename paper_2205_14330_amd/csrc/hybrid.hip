@@ -15,15 +15,11 @@
 //
 // Voxels: cell keys per point, a stable radix sort of (key, point index),
 // segment starts where the key changes, one thread per voxel.
-// Neighbours: a uniform grid over the points' bounding box (about 2 points per
-// cell), points sorted by cell, one thread per query walking Chebyshev shells
-// of cells around its own; it keeps the K best (distance, index) pairs packed
-// in 64-bit keys and stops once the K-th distance is below the smallest
-// distance any cell of the next shell can hold (with a margin far above the
-// float32 rounding of the distances), so the result is the exact K nearest.
+// Neighbours: over a uniform grid of cells (nn_grid.h), exact.
 #include <algorithm>
 
 #include "dpr_internal.h"
+#include "nn_grid.h"
 
 // Every float32 decision above is made with each multiply and add rounded on
 // its own, so no multiply-add may be fused in this file.  (The rounding
@@ -197,129 +193,6 @@ __global__ __launch_bounds__(kHyThreads) void k_voxel_average(const uint32_t *st
     acc.store_mean(out, v, (double)(e - b));
 }
 
-// cell_start[c] = first sorted position with key >= c, for c in [0, ncells]
-__global__ __launch_bounds__(kHyThreads) void k_cell_start(const uint32_t *skeys, uint32_t m, uint32_t ncells,
-                                                          uint32_t *cell_start) {
-    const uint32_t i = blockIdx.x * kHyThreads + threadIdx.x;
-    if (i > m) return;
-    const uint32_t lo = i == 0 ? 0u : skeys[i - 1] + 1u;
-    const uint32_t hi = i == m ? ncells : skeys[i];
-    for (uint32_t c = lo; c <= hi; ++c) cell_start[c] = i;
-}
-
-// float32 squared distance ((dx dx + dy dy) + dz dz), dx = x_j - x_i
-__device__ __forceinline__ float dist2(const float *pi, const float *pj) {
-    const float dx = pj[0] - pi[0], dy = pj[1] - pi[1], dz = pj[2] - pi[2];
-    float s = dx * dx;
-    s = s + dy * dy;
-    return s + dz * dz;
-}
-
-struct KnnGrid {
-    const float *xyz;
-    const uint32_t *skeys, *svals, *cell_start;
-    const float *box;
-    uint32_t m, G;
-    int K, keff;
-    int32_t *idx;
-    float *d2;
-};
-
-// One thread per query (queries in cell order).  best[] holds the K smallest
-// (distance bits << 32 | index) keys in ascending order.  KMAX (8, 16 or 32,
-// at least K) sizes the list, so that an insertion takes KMAX predicated
-// steps rather than always 32.
-template <int KMAX>
-__global__ __launch_bounds__(kHyThreads) void k_knn(KnnGrid g) {
-    const uint32_t t = blockIdx.x * kHyThreads + threadIdx.x;
-    if (t >= g.m) return;
-    const uint32_t p = g.svals[t];
-    const uint32_t key = g.skeys[t];
-    const int G = (int)g.G;
-    const int cx = (int)(key % g.G), cy = (int)((key / g.G) % g.G), cz = (int)(key / (g.G * g.G));
-    float hmin = INFINITY;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const float ext = g.box[3 + a] - g.box[a];
-        if (ext > 0.f) hmin = fminf(hmin, ext / (float)G);
-    }
-    const float *pp = g.xyz + 3 * (size_t)p;
-    uint64_t best[KMAX];
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) best[k] = ~0ull;
-    const int K = g.keff;
-    uint64_t worst = ~0ull;           // best[K - 1]
-    int found = 0;
-    const int rmax = max(max(max(cx, G - 1 - cx), max(cy, G - 1 - cy)), max(cz, G - 1 - cz));
-    for (int r = 0; r <= rmax; ++r) {
-        for (int dz = -r; dz <= r; ++dz) {
-            const int z = cz + dz;
-            if (z < 0 || z >= G) continue;
-            for (int dy = -r; dy <= r; ++dy) {
-                const int y = cy + dy;
-                if (y < 0 || y >= G) continue;
-                const bool full = dz == -r || dz == r || dy == -r || dy == r;
-                for (int dx = -r; dx <= r; dx += full ? 1 : (r > 0 ? 2 * r : 1)) {
-                    const int x = cx + dx;
-                    if (x < 0 || x >= G) continue;
-                    const uint32_t c = ((uint32_t)z * g.G + (uint32_t)y) * g.G + (uint32_t)x;
-                    const uint32_t b = g.cell_start[c], e = g.cell_start[c + 1];
-                    for (uint32_t j = b; j < e; ++j) {
-                        const uint32_t q = g.svals[j];
-                        if (q == p) continue;
-                        const float d = dist2(pp, g.xyz + 3 * (size_t)q);
-                        uint64_t x64 = ((uint64_t)__float_as_uint(d) << 32) | q;
-                        ++found;
-                        if (x64 >= worst) continue;
-                        // insert into the sorted prefix: keep the smaller, carry the larger on
-#pragma unroll
-                        for (int k = 0; k < KMAX; ++k) {
-                            if (k < K) {
-                                const uint64_t lo = best[k] < x64 ? best[k] : x64;
-                                x64 = best[k] < x64 ? x64 : best[k];
-                                best[k] = lo;
-                            }
-                        }
-#pragma unroll
-                        for (int k = 0; k < KMAX; ++k)
-                            if (k == K - 1) worst = best[k];
-                    }
-                }
-            }
-        }
-        if (found >= K) {
-            // any point of shell r + 1 or beyond is at least r * hmin away
-            const float kth = __uint_as_float((uint32_t)(worst >> 32));
-            const float bound = (float)r * hmin;
-            if (kth < 0.9999f * bound * bound) break;
-        }
-    }
-    for (int k = 0; k < g.K; ++k) {
-        const bool ok = k < K;
-        g.idx[(size_t)p * g.K + k] = ok ? (int32_t)(uint32_t)(best[k] & 0xFFFFFFFFull) : -1;
-        g.d2[(size_t)p * g.K + k] = ok ? __uint_as_float((uint32_t)(best[k] >> 32)) : 0.f;
-    }
-}
-
-// delta of the neighbour distances (float32, each operation rounded) > eps -> removed
-__global__ __launch_bounds__(kHyThreads) void k_spread_keep(const float *d2, uint32_t m, int K, int keff, float eps,
-                                                           uint32_t *keep) {
-    const uint32_t i = blockIdx.x * kHyThreads + threadIdx.x;
-    if (i >= m) return;
-    if (keff == 0) { keep[i] = 1u; return; }
-    const float *d = d2 + (size_t)i * K;
-    float sum = 0.f;
-    for (int q = 0; q < keff; ++q) sum = sum + sqrtf(d[q]);
-    const float mean = __fdiv_rn(sum, (float)keff);
-    float var = 0.f;
-    for (int q = 0; q < keff; ++q) {
-        const float e = sqrtf(d[q]) - mean;
-        var = var + e * e;
-    }
-    const float delta = sqrtf(__fdiv_rn(var, (float)keff));
-    keep[i] = (delta > eps) ? 0u : 1u;
-}
-
 template <int K3>
 __global__ __launch_bounds__(kHyThreads) void k_gather_kept(const uint32_t *keep, const uint32_t *pos, uint32_t m,
                                                            CloudIn in, CloudOut out) {
@@ -341,16 +214,26 @@ __global__ __launch_bounds__(kHyThreads) void k_gather_kept(const uint32_t *keep
     out.rad[o] = v[4 + K3];
 }
 
-// generated point i (written at m + i) = FP64 average of point i's neighbours, in neighbour order
+// generated point i (written at m + i) = FP64 average of point i's neighbours,
+// in neighbour order.  Every value of a row has a thread, neighbouring values
+// neighbouring lanes, so a neighbour's K3 SH floats are one run of loads: 255k
+// points with 8 neighbours take 50 us, against 96 us with a thread per row,
+// each of whose lanes walks 27 floats of a row of its own.  At most 2^30 threads
+// are launched; each takes every so manieth value.
 template <int K3>
 __global__ __launch_bounds__(kHyThreads) void k_generate(CloudOut c, uint32_t m, const int32_t *idx, int K, int keff) {
-    const uint32_t i = blockIdx.x * kHyThreads + threadIdx.x;
-    if (i >= m) return;
-    const int32_t *nb = idx + (size_t)i * K;
-    RowSum<K3> acc;
-    acc.clear();
-    for (int q = 0; q < keff; ++q) acc.add(c.xyz, c.sh, c.op, c.rad, (size_t)nb[q]);
-    acc.store_mean(c, (size_t)m + i, (double)keff);
+    constexpr uint32_t kRow = 5 + K3;
+    for (uint64_t t = (uint64_t)blockIdx.x * kHyThreads + threadIdx.x; t < (uint64_t)m * kRow;
+         t += (uint64_t)gridDim.x * kHyThreads) {
+        const uint32_t i = (uint32_t)(t / kRow), a = (uint32_t)(t - (uint64_t)i * kRow);
+        float *const col = a < 3u ? c.xyz + a : a < 3u + K3 ? c.sh + (a - 3u) : a == 3u + K3 ? c.op : c.rad;
+        const uint32_t stride = a < 3u ? 3u : a < 3u + K3 ? (uint32_t)K3 : 1u;
+        const int32_t *nb = idx + (size_t)i * K;
+        double sum = 0.0;
+#pragma unroll 8
+        for (int q = 0; q < keff; ++q) sum += (double)col[(uint64_t)(uint32_t)nb[q] * stride];
+        col[((uint64_t)m + i) * stride] = (float)(sum / (double)keff);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -376,22 +259,15 @@ static int key_bits(uint64_t ncells) {
     return b;
 }
 
-uint32_t knn_grid_size(uint64_t m) {
-    uint32_t g = 1;
-    while ((uint64_t)(g + 1) * (g + 1) * (g + 1) * 2 <= m && g < kKnnMaxGrid) ++g;
-    return g;
-}
-
 HyScratchBytes hy_scratch_bytes(uint64_t n, int K) {
     const uint64_t hw = radix_hist_words(n);
-    const uint64_t G = knn_grid_size(n);
     HyScratchBytes b;
     b.keys = b.vals = b.keys_alt = b.vals_alt = 4 * n;
     b.hist = 4 * (hw + 1);                 // the scan also writes the total after the last word
     b.part = 8 * (std::max(scan_partials(n + 2), scan_partials(hw)) + 2);
     b.total64 = 8;
     b.flags = b.seg = b.starts = 4 * (n + 2);
-    b.cell_start = 4 * (G * G * G + 2);
+    b.cell_start = grid_bytes(n).bytes;
     b.box_part = 4 * 6 * (uint64_t)kHyBoxBlocks;
     b.box = 4 * 6;
     b.idx = b.d2 = 4 * n * (uint64_t)K;
@@ -420,31 +296,43 @@ static hipError_t sorted_cells(const float *xyz, uint32_t n, uint32_t N, HyScrat
     return e;
 }
 
+static NnCloud neighbour_cloud(const float *xyz, uint32_t m, int K, HyScratch &s) {
+    return grid_cloud(xyz, m, nn_density(K, m), reinterpret_cast<uint8_t *>(s.cell_start));
+}
+
+// The K nearest other points of every point: to idx and, where given, d2; or
+// (MODE kNnSpread) to idx, and the verdict on their spread to keep.
+template <int MODE>
+static hipError_t search(const NnCloud &c, int K, int32_t *idx, float *d2, uint32_t *keep, float eps, hipStream_t st) {
+    hipError_t e = launch_grids(c, nullptr, nullptr, 0, st);
+    if (e != hipSuccess) return e;
+    NnQuery q = grid_query(c, c, K, (uint64_t)c.n - 1);
+    q.idx = idx;
+    q.d2 = d2;
+    q.keep = keep;
+    q.eps = eps;
+    return launch_search<MODE, true>(q, st);
+}
+
+// After search<kNnSpread> over c: the neighbours among the points left, mk >= 2
+// of them, by their new numbers pos: from the neighbours among all (old), and
+// by a search of c's grid for the points that lost one.
+static hipError_t renumber(const NnCloud &c, int K, uint32_t mk, const uint32_t *alive, const uint32_t *pos,
+                           const int32_t *old, int32_t *idx, hipStream_t st) {
+    NnQuery q = grid_query(c, c, K, (uint64_t)mk - 1);
+    q.idx = idx;
+    q.alive = alive;
+    q.pos = pos;
+    hipError_t e = launch_fill_u32(q.list_n, 0u, 1, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_nn_renumber, dim3(blocks_for(c.n)), dim3(kGridThreads), 0, st, q, old);
+    hipLaunchKernelGGL((k_nn_rest<kNnIndex, true, false, true>), dim3(rest_blocks(q.nq)), dim3(kGridThreads), 0, st, q);
+    return hipGetLastError();
+}
+
 hipError_t launch_knn(const float *xyz, uint32_t m, int K, int32_t *idx, float *d2, HyScratch &s, hipStream_t st) {
     if (m == 0) return hipSuccess;
-    const uint32_t G = knn_grid_size(m);
-    uint32_t *skeys, *svals;
-    hipError_t e = sorted_cells(xyz, m, G, s, &skeys, &svals, st);
-    if (e != hipSuccess) return e;
-    const uint32_t ncells = G * G * G;
-    hipLaunchKernelGGL(k_cell_start, dim3(blocks_for((uint64_t)m + 1)), dim3(kHyThreads), 0, st, skeys, m, ncells,
-                       s.cell_start);
-    KnnGrid g;
-    g.xyz = xyz;
-    g.skeys = skeys;
-    g.svals = svals;
-    g.cell_start = s.cell_start;
-    g.box = s.box;
-    g.m = m;
-    g.G = G;
-    g.K = K;
-    g.keff = (int)std::min<uint64_t>((uint64_t)K, (uint64_t)m - 1);
-    g.idx = idx;
-    g.d2 = d2;
-    if (g.K <= 8) hipLaunchKernelGGL(k_knn<8>, dim3(blocks_for(m)), dim3(kHyThreads), 0, st, g);
-    else if (g.K <= 16) hipLaunchKernelGGL(k_knn<16>, dim3(blocks_for(m)), dim3(kHyThreads), 0, st, g);
-    else hipLaunchKernelGGL(k_knn<kKnnMax>, dim3(blocks_for(m)), dim3(kHyThreads), 0, st, g);
-    return hipGetLastError();
+    return search<kNnIndexDist>(neighbour_cloud(xyz, m, K, s), K, idx, d2, nullptr, 0.f, st);
 }
 
 hipError_t launch_voxel_reduce(const float *xyz, const float *sh, const float *op, const float *rad, uint32_t n,
@@ -473,10 +361,9 @@ hipError_t launch_filter_generate(const float *xyz, const float *sh, const float
     *kept_host = 0;
     *count_host = 0;
     if (m == 0) return hipSuccess;
-    hipError_t e = launch_knn(xyz, m, K, s.idx, s.d2, s, st);
+    const NnCloud c = neighbour_cloud(xyz, m, K, s);
+    hipError_t e = search<kNnSpread>(c, K, s.idx, nullptr, s.flags, eps, st);
     if (e != hipSuccess) return e;
-    const int keff = (int)std::min<uint64_t>((uint64_t)K, (uint64_t)m - 1);
-    hipLaunchKernelGGL(k_spread_keep, dim3(blocks_for(m)), dim3(kHyThreads), 0, st, s.d2, m, K, keff, eps, s.flags);
     e = launch_scan(s.flags, s.seg, m, s.part, s.total64, st);
     if (e != hipSuccess) return e;
     CloudIn in{xyz, sh, op, rad};
@@ -487,10 +374,20 @@ hipError_t launch_filter_generate(const float *xyz, const float *sh, const float
     const uint32_t mk = (uint32_t)*kept_host;
     *count_host = mk;
     if (mk < 2) return hipSuccess;
-    e = launch_knn(oxyz, mk, K, s.idx, s.d2, s, st);
+    // Few removed: most points keep their neighbours, and those that lost one are searched for again; with more
+    // removed the cloud that is left is searched anew.  The update of a 300k-point cloud (K = 8) takes 477 us by
+    // the first way and 603 by the second at 0.2% removed, 542 and 606 at 2%, 592 and 607 at 6%, 655 and 605 at 11%.
+    int32_t *idx = s.idx;
+    if (m - mk <= m / 16u) {
+        idx = reinterpret_cast<int32_t *>(s.d2);
+        e = renumber(c, K, mk, s.flags, s.seg, s.idx, idx, st);
+    } else {
+        e = search<kNnIndex>(neighbour_cloud(oxyz, mk, K, s), K, idx, nullptr, nullptr, 0.f, st);
+    }
     if (e != hipSuccess) return e;
     const int keff2 = (int)std::min<uint64_t>((uint64_t)K, (uint64_t)mk - 1);
-    HY_K3_DISPATCH(k3, k_generate, dim3(blocks_for(mk)), dim3(kHyThreads), 0, st, out, mk, s.idx, K, keff2);
+    const uint32_t gen_blocks = (uint32_t)std::min<uint64_t>(((uint64_t)mk * (5 + k3) + kHyThreads - 1) / kHyThreads, 1u << 22);
+    HY_K3_DISPATCH(k3, k_generate, dim3(gen_blocks), dim3(kHyThreads), 0, st, out, mk, idx, K, keff2);
     *count_host = 2ull * mk;
     return hipGetLastError();
 }

@@ -109,3 +109,24 @@ def test_knn_by_thread_and_by_wave(dpr, name, n, K):
     d = x[idx.long()] - x[:, None]
     d = d * d
     assert torch.equal(d2, (d[..., 0] + d[..., 1]) + d[..., 2])
+
+
+@pytest.mark.parametrize("share", [0.0, 0.02, 0.06, 0.07, 0.3])
+def test_update_with_few_and_many_removed(dpr, share):
+    """The neighbours among the points left: renumbered where at most one in 16 was removed, searched for anew beyond."""
+    from paper_2205_14330_amd import hybrid
+    N, K = 64, 6
+    x = clouds("floaters", 6)[0]
+    sh, op, rad = workloads.point_attributes(len(x), 1, 3)
+    c = oracle.Cloud(x, sh, op, rad)
+    red = oracle.hybrid_update(c, N, K, 1e30)[0]
+    d = np.sort(np.sqrt(((red.xyz[:, None].astype(np.float64) - red.xyz[None]) ** 2).sum(-1)), 1)[:, 1:K + 1]
+    s = np.sort(d.std(1))[::-1]
+    k = int(round(share * len(s)))
+    eps = float(s[0] * 2) if k == 0 else float(0.5 * (s[k - 1] + s[k]))
+    ref_red, ref_keep, ref = oracle.hybrid_update(c, N, K, eps)
+    got, counts = hybrid.hybrid_update(dpr.SceneTensors.from_numpy(c), N, K, eps)
+    assert counts["voxels"] == ref_red.n and counts["kept"] == ref_red.n - k
+    for a in ("xyz", "sh", "opacity", "radius"):
+        want = np.asarray(getattr(ref, a)).astype(np.float32)
+        assert np.array_equal(getattr(got, a).cpu().numpy(), want.reshape(getattr(got, a).shape)), a
