@@ -60,12 +60,13 @@ struct Sizes {
     uint64_t items = 0, tiles = 0, pixels = 0, chunks = 0, cnt = 0, sort_blocks = 0, point_blocks = 0;
     uint64_t max_view_tiles = 0, max_view_segs = 0, segs = 0;
     int32_t sh_degree = 0;
+    bool one_block_views = true;      // no view has more items than one block of the depth sort
 };
 
 struct PlanLayout {
-    Region views, scenes, u32tab, rec, keys, vals, keys_alt, vals_alt, rect, bin, hist, part, cnt, segs, tile_total,
+    Region views, scenes, u32tab, rec, keys, vals, keys_alt, vals_alt, rect, bin, total, cnt, segs, tile_total,
         tile_base, tile_order, bucket_cnt, block_sum;
-    uint64_t total = 0;
+    uint64_t bytes = 0;
 };
 
 PlanLayout plan_layout(const Sizes &s) {
@@ -82,10 +83,7 @@ PlanLayout plan_layout(const Sizes &s) {
     p.vals_alt = L.add(4 * s.items);
     p.rect = L.add(8 * s.items);
     p.bin = L.add(sizeof(BinRec) * s.items);
-    const uint64_t nh = 256ull * s.sort_blocks;
-    p.hist = L.add(4 * (nh + 1));
-    const uint64_t np = std::max(scan_partials(nh), scan_partials(s.tiles)) + 2;
-    p.part = L.add(8 * np);
+    p.total = L.add(8);
     p.cnt = L.add(4 * s.cnt);
     p.segs = L.add(4 * s.segs);
     p.tile_total = L.add(4 * s.tiles);
@@ -93,7 +91,7 @@ PlanLayout plan_layout(const Sizes &s) {
     p.tile_order = L.add(4 * s.tiles);
     p.bucket_cnt = L.add(4ull * kOrderBuckets * order_count_blocks(s.tiles));
     p.block_sum = L.add(8ull * order_count_blocks(s.tiles));
-    p.total = L.total;
+    p.bytes = L.total;
     return p;
 }
 
@@ -160,6 +158,7 @@ int check_inputs(const dpr_scene *scenes, int32_t n_scenes, const dpr_view *view
         s.segs += tx * ty * nseg;
         s.max_view_segs = std::max(s.max_view_segs, nseg);
         s.sort_blocks += (n + kDepthSortTile - 1) / kDepthSortTile;
+        s.one_block_views = s.one_block_views && n <= (uint64_t)kDepthSortTile;
     }
     if (s.items >= 0x7FFFFFFFull) return fail(DPR_ERR_UNSUPPORTED, "total view-points must be < 2^31");
     if (s.tiles >= 0xFFFFFFFFull || s.cnt >= 0xFFFFFFFFull || s.chunks >= 0xFFFFFFFFull)
@@ -472,7 +471,7 @@ const char *dpr_last_error(void) { return g_err.c_str(); }
 size_t dpr_plan_ws_bytes(const dpr_scene *scenes, int32_t n_scenes, const dpr_view *views, int32_t n_views) {
     Sizes s;
     if (check_inputs(scenes, n_scenes, views, n_views, &s) != DPR_OK) return 0;
-    return (size_t)plan_layout(s).total;
+    return (size_t)plan_layout(s).bytes;
 }
 
 namespace {
@@ -495,8 +494,8 @@ int plan_forward_impl(const dpr_scene *scenes, int32_t n_scenes, const dpr_view 
     rc = check_inputs(scenes, n_scenes, views, n_views, &s);
     if (rc) return rc;
     const PlanLayout lay = plan_layout(s);
-    if (!plan_ws || plan_ws_bytes < lay.total)
-        return fail(DPR_ERR_WORKSPACE, "plan workspace needs %llu bytes, got %llu", (unsigned long long)lay.total,
+    if (!plan_ws || plan_ws_bytes < lay.bytes)
+        return fail(DPR_ERR_WORKSPACE, "plan workspace needs %llu bytes, got %llu", (unsigned long long)lay.bytes,
                     (unsigned long long)plan_ws_bytes);
     if (fault_injected("launch")) return fail(DPR_ERR_HIP, "injected launch failure (DPR_FAULT=launch)");
 
@@ -567,7 +566,7 @@ int plan_forward_impl(const dpr_scene *scenes, int32_t n_scenes, const dpr_view 
         }
     }
     {
-        uint64_t item = 0, tile = 0, chunk = 0, sblk = 0, hist = 0, cnt = 0, seg = 0, pix = 0;
+        uint64_t item = 0, tile = 0, chunk = 0, sblk = 0, cnt = 0, seg = 0, pix = 0;
         for (int v = 0; v < V; ++v) {
             const dpr_view &vw = views[v];
             ViewDesc &d = p->vdesc[v];
@@ -589,7 +588,6 @@ int plan_forward_impl(const dpr_scene *scenes, int32_t n_scenes, const dpr_view 
             d.nchunks = (uint32_t)(((uint64_t)sc.n + kChunkItems - 1) / kChunkItems);
             d.sort_block_off = (uint32_t)sblk;
             d.nsort_blocks = (uint32_t)(((uint64_t)sc.n + kDepthSortTile - 1) / kDepthSortTile);
-            d.hist_off = hist;
             d.cnt_off = cnt;
             d.seg_off = seg;
             d.pix_off = pix;
@@ -604,7 +602,6 @@ int plan_forward_impl(const dpr_scene *scenes, int32_t n_scenes, const dpr_view 
             tile += nt;
             chunk += d.nchunks;
             sblk += d.nsort_blocks;
-            hist += 256ull * d.nsort_blocks;
             cnt += nt * d.nchunks;
             seg += nt * ((d.nchunks + kSegChunks - 1) / kSegChunks);
             pix += (uint64_t)d.width * d.height;
@@ -619,14 +616,12 @@ int plan_forward_impl(const dpr_scene *scenes, int32_t n_scenes, const dpr_view 
     uint32_t *keys_alt = reinterpret_cast<uint32_t *>(w + lay.keys_alt.off);
     uint32_t *vals_alt = reinterpret_cast<uint32_t *>(w + lay.vals_alt.off);
     uint2 *rect = reinterpret_cast<uint2 *>(w + lay.rect.off);
-    uint32_t *hist = reinterpret_cast<uint32_t *>(w + lay.hist.off);
-    uint64_t *part = reinterpret_cast<uint64_t *>(w + lay.part.off);
+    uint32_t *scratch = reinterpret_cast<uint32_t *>(w + lay.bin.off);     // of the sort, before the binning records
     uint32_t *cnt = reinterpret_cast<uint32_t *>(w + lay.cnt.off);
     uint32_t *segs = reinterpret_cast<uint32_t *>(w + lay.segs.off);
     uint32_t *tile_total = reinterpret_cast<uint32_t *>(w + lay.tile_total.off);
     uint32_t *tile_base = reinterpret_cast<uint32_t *>(w + lay.tile_base.off);
-    const uint64_t np = lay.part.bytes / 8;
-    uint64_t *total64 = part + np - 1;
+    uint64_t *total64 = reinterpret_cast<uint64_t *>(w + lay.total.off);
 
 #define STAGE_TRY(expr)                                                                           \
     do {                                                                                          \
@@ -648,12 +643,13 @@ int plan_forward_impl(const dpr_scene *scenes, int32_t n_scenes, const dpr_view 
     }
     {
         StageScope sc_(p, DPR_STAGE_PROJECT, st);
-        STAGE_TRY(launch_project(tb, p->th, s.sh_degree, (uint32_t)s.point_blocks, rec, keys, vals, rect, st));
+        STAGE_TRY(launch_project(tb, p->th, s.sh_degree, (uint32_t)s.point_blocks, rec, keys_alt, rect, scratch,
+                                 st));
     }
     {
         StageScope sc_(p, DPR_STAGE_DEPTH_SORT, st);
-        STAGE_TRY(launch_depth_sort(tb, (uint32_t)s.sort_blocks, (uint32_t)s.items, keys, vals, keys_alt, vals_alt,
-                                    hist, part, st));
+        STAGE_TRY(launch_depth_sort(tb, (uint32_t)s.sort_blocks, s.one_block_views, keys, vals, keys_alt, vals_alt,
+                                    scratch, st));
     }
     {
         StageScope sc_(p, DPR_STAGE_TILE_COUNT, st);
@@ -884,7 +880,7 @@ int dpr_plan_get_info(const dpr_plan *p, dpr_plan_info *out) {
     out->tiles = (int64_t)p->sz.tiles;
     out->pixels = (int64_t)p->sz.pixels;
     out->chunks = (int64_t)p->sz.chunks;
-    out->plan_ws_bytes = (int64_t)p->lay.total;
+    out->plan_ws_bytes = (int64_t)p->lay.bytes;
     out->fwd_ws_bytes = (int64_t)f.total;
     out->bwd_ws_bytes = (int64_t)bwd_layout(p).total;
     out->rec_off = (int64_t)p->lay.rec.off;

@@ -19,6 +19,8 @@ constexpr int kSortItemsPerThread = 8;
 constexpr int kSortTile = kSortThreads * kSortItemsPerThread;   // 2048 keys per sort block
 constexpr int kDepthSortThreads = 1024;
 constexpr int kDepthSortTile = 8 * kDepthSortThreads;              // 8192 keys per depth-sort block
+constexpr int kSortPasses = 3;
+constexpr uint32_t kSortMaxBins = 2048;   // digits of at most 11 bits
 constexpr int kScanThreads = 256;
 constexpr int kScanItemsPerThread = 8;
 constexpr int kScanTile = kScanThreads * kScanItemsPerThread;   // 2048 elements per scan block
@@ -44,7 +46,6 @@ struct ViewDesc {
     uint32_t sort_block_off;    // first depth-sort block of this view
     uint32_t nsort_blocks;
     uint32_t pad0;
-    uint64_t hist_off;          // first radix-histogram entry of this view
     uint64_t cnt_off;           // first (chunk, tile) count entry of this view (chunk-major)
     uint64_t seg_off;           // first (segment, tile) partial-sum entry of this view
     uint64_t pix_off;           // first pixel of this view in per-pixel state arrays
@@ -99,6 +100,33 @@ struct __align__(16) BinRec {
     float thr;              // w + lambda, the bound of the (splat, tile) test
     float px, py, a, b;     // centre and axis coefficients of the splat record
 };
+
+// Scratch of the depth sort: the view's part of the binning records (8 words
+// per item), which are written after the sort.
+struct SortScratch {
+    uint32_t *range;            // [2 groups of 64 points] smallest and largest key
+    uint32_t *par;              // kmin, largest distance (a dropped item's), digit bits
+    uint32_t *total;            // [3][kSortMaxBins]
+    uint32_t *ticket;           // [3], behind total
+    uint32_t *pub;              // [3][blocks][kSortMaxBins]
+};
+__device__ __forceinline__ SortScratch sort_scratch(uint32_t *scratch, const ViewDesc &vd) {
+    uint32_t *const w = scratch + 8ull * vd.item_off;
+    const uint64_t nb = ((uint64_t)vd.n + 63) / 64;
+    SortScratch s;
+    s.range = w;
+    s.par = w + 2 * nb;
+    s.total = s.par + 4;
+    s.ticket = s.total + kSortPasses * kSortMaxBins;
+    s.pub = s.ticket + 4;
+    return s;
+}
+// The scratch fits the 8 words per item: in a view of more than one block
+// (n > (blocks - 1) 8192) the counts take less than a word per item.
+static_assert(2 + 4 <= 8, "a view of one item");
+static_assert((uint64_t)kSortPasses * kSortMaxBins + 2 * (kDepthSortTile / 64 + 1) + 8 + 2ull * kSortPasses * kSortMaxBins <=
+                  8ull * kDepthSortTile,
+              "two blocks");
 
 // Index of the segment containing x: largest s < n with starts[s] <= x.
 __device__ __forceinline__ int find_segment(const uint32_t *starts, int n, uint32_t x) {
@@ -199,14 +227,14 @@ struct Tables {                  // device pointers inside the plan workspace
 };
 
 hipError_t launch_project(const Tables &tb, const Thresholds &th, int sh_degree, uint32_t point_blocks,
-                          SplatRec *rec, uint32_t *keys, uint32_t *vals, uint2 *rect,
-                          hipStream_t st);
+                          SplatRec *rec, uint32_t *keys, uint2 *rect, uint32_t *sort_scratch, hipStream_t st);
 
-// Segmented (per view) stable LSD radix sort of 32-bit keys with 32-bit values.
-// Scratch: hist[256 * sort_blocks + 1] u32, part[] u64 (scan partials).
-hipError_t launch_depth_sort(const Tables &tb, uint32_t sort_blocks, uint32_t items,
-                             uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint32_t *vals_alt,
-                             uint32_t *hist, uint64_t *part, hipStream_t st);
+// Stable sort of every view's items by depth key: from keys_alt (the keys in
+// item order) to keys and vals (the item ids); vals_alt and scratch (the
+// binning records' place, prepared by the projection) are overwritten.
+// one_block_views: no view has more than kDepthSortTile items.
+hipError_t launch_depth_sort(const Tables &tb, uint32_t sort_blocks, bool one_block_views, uint32_t *keys,
+                             uint32_t *vals, uint32_t *keys_alt, uint32_t *vals_alt, uint32_t *scratch, hipStream_t st);
 
 // Exclusive scan of n u32 counts into out[0..n] (out[n] = total mod 2^32);
 // the exact 64-bit total goes to *total64.  part: >= scan_partials(n) u64.

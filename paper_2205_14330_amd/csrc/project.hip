@@ -14,9 +14,24 @@ namespace dpr {
 
 constexpr int kProjThreads = 128;
 
+// Minimum and maximum of the wave's values, in its last lane.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void range_step(uint32_t &lo, uint32_t &hi) {
+    lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, CTRL, ROWS, 0xF, false));
+    hi = max(hi, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, CTRL, ROWS, 0xF, false));
+}
+__device__ __forceinline__ void wave_range(uint32_t &lo, uint32_t &hi) {
+    range_step<0x111, 0xF>(lo, hi);      // from the lane 1, 2, 4, 8 below in the row of 16
+    range_step<0x112, 0xF>(lo, hi);
+    range_step<0x114, 0xF>(lo, hi);
+    range_step<0x118, 0xF>(lo, hi);
+    range_step<0x142, 0xA>(lo, hi);      // lane 15 of the row below, then lane 31 of the half below
+    range_step<0x143, 0xC>(lo, hi);
+}
+
 template <int DEG>
 __global__ __launch_bounds__(kProjThreads) void k_project(Tables tb, Thresholds th, SplatRec *rec,
-                                                          uint32_t *keys, uint32_t *vals, uint2 *rect) {
+                                                          uint32_t *keys, uint2 *rect, uint32_t *sort_words) {
     extern __shared__ float s_sh[];
     const int s = find_segment(tb.scene_block_start, tb.n_scenes, blockIdx.x);
     const SceneDesc sc = tb.scenes[s];
@@ -50,15 +65,16 @@ __global__ __launch_bounds__(kProjThreads) void k_project(Tables tb, Thresholds 
         }
     }
     __syncthreads();
-    if (i >= sc.n) return;
-
-    const float x = sc.xyz[3 * (size_t)i + 0];
-    const float y = sc.xyz[3 * (size_t)i + 1];
-    const float z = sc.xyz[3 * (size_t)i + 2];
-    const float o = sc.opacity[i];
-    const float r = sc.radius[i];
+    if ((i & ~63) >= sc.n) return;       // the whole wave is past the end
+    const bool in = i < sc.n;
+    const int ic = in ? i : sc.n - 1;
+    const float x = sc.xyz[3 * (size_t)ic + 0];
+    const float y = sc.xyz[3 * (size_t)ic + 1];
+    const float z = sc.xyz[3 * (size_t)ic + 2];
+    const float o = sc.opacity[ic];
+    const float r = sc.radius[ic];
     const float log2o = __log2f(o);
-    const float *h = s_sh + threadIdx.x * stride;
+    const float *h = s_sh + (in ? threadIdx.x : 0u) * stride;
 
     for (uint32_t vv = 0; vv < sc.view_count; ++vv) {
         const ViewDesc &vd = tb.views[tb.scene_views[sc.view_start + vv]];
@@ -123,26 +139,36 @@ __global__ __launch_bounds__(kProjThreads) void k_project(Tables tb, Thresholds 
                 }
             }
         }
-        float4 *dst = reinterpret_cast<float4 *>(rec + g);
-        dst[0] = make_float4(out.px, out.py, out.a, out.b);
-        dst[1] = make_float4(out.w, out.cr, out.cg, out.cb);
-        keys[g] = key;
-        vals[g] = g;
-        rect[g] = rc;
+        if (in) {
+            float4 *dst = reinterpret_cast<float4 *>(rec + g);
+            dst[0] = make_float4(out.px, out.py, out.a, out.b);
+            dst[1] = make_float4(out.w, out.cr, out.cg, out.cb);
+            keys[g] = key;
+            rect[g] = rc;
+        }
+        // for the depth sort: the range of the wave's keys, and cleared totals
+        const SortScratch ss = sort_scratch(sort_words, vd);
+        const bool kept = in && key != kDroppedKey;
+        uint32_t lo = kept ? key : 0xFFFFFFFFu, hi = kept ? key : 0u;
+        wave_range(lo, hi);
+        if ((threadIdx.x & 63u) == 63u) {
+            ss.range[2 * (i >> 6)] = lo;
+            ss.range[2 * (i >> 6) + 1] = hi;
+        }
+        if (vd.nsort_blocks > 1u && in && i < (int)(kSortPasses * kSortMaxBins + 4u)) ss.total[i] = 0u;
     }
 }
 
 hipError_t launch_project(const Tables &tb, const Thresholds &th, int sh_degree, uint32_t point_blocks,
-                          SplatRec *rec, uint32_t *keys, uint32_t *vals, uint2 *rect,
-                          hipStream_t st) {
+                          SplatRec *rec, uint32_t *keys, uint2 *rect, uint32_t *sort_words, hipStream_t st) {
     if (point_blocks == 0) return hipSuccess;
     const int row = 3 * (sh_degree + 1) * (sh_degree + 1);
     const size_t lds = (size_t)kProjThreads * (row | 1) * sizeof(float);
     switch (sh_degree) {
-    case 0: hipLaunchKernelGGL(k_project<0>, dim3(point_blocks), dim3(kProjThreads), lds, st, tb, th, rec, keys, vals, rect); break;
-    case 1: hipLaunchKernelGGL(k_project<1>, dim3(point_blocks), dim3(kProjThreads), lds, st, tb, th, rec, keys, vals, rect); break;
-    case 2: hipLaunchKernelGGL(k_project<2>, dim3(point_blocks), dim3(kProjThreads), lds, st, tb, th, rec, keys, vals, rect); break;
-    case 3: hipLaunchKernelGGL(k_project<3>, dim3(point_blocks), dim3(kProjThreads), lds, st, tb, th, rec, keys, vals, rect); break;
+    case 0: hipLaunchKernelGGL(k_project<0>, dim3(point_blocks), dim3(kProjThreads), lds, st, tb, th, rec, keys, rect, sort_words); break;
+    case 1: hipLaunchKernelGGL(k_project<1>, dim3(point_blocks), dim3(kProjThreads), lds, st, tb, th, rec, keys, rect, sort_words); break;
+    case 2: hipLaunchKernelGGL(k_project<2>, dim3(point_blocks), dim3(kProjThreads), lds, st, tb, th, rec, keys, rect, sort_words); break;
+    case 3: hipLaunchKernelGGL(k_project<3>, dim3(point_blocks), dim3(kProjThreads), lds, st, tb, th, rec, keys, rect, sort_words); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
