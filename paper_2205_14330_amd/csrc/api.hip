@@ -190,6 +190,11 @@ struct dpr_plan {
     std::vector<ViewDesc> vdesc;
     std::vector<SceneDesc> sdesc;
     std::vector<uint32_t> u32tab;
+    // place of a scene in sdesc: the scenes with views first, so that their
+    // point blocks come first and the projection launches no others (a server
+    // keeps many scenes resident and renders a few at a time)
+    std::vector<int32_t> scene_slot;
+    uint64_t viewed_blocks = 0;
     std::vector<uint32_t> up_img;   // the upload image of views, scenes and u32tab
     uint8_t *pws = nullptr;
     uint64_t pairs = 0;
@@ -543,9 +548,19 @@ int plan_forward_impl(const dpr_scene *scenes, int32_t n_scenes, const dpr_view 
     {
         std::vector<uint32_t> count(S, 0);
         for (int v = 0; v < V; ++v) count[views[v].scene]++;
+        p->scene_slot.resize(S);
+        std::vector<int32_t> slots;                       // the scene of each slot
+        slots.reserve(S);
+        for (int viewed = 1; viewed >= 0; --viewed)
+            for (int sidx = 0; sidx < S; ++sidx)
+                if ((count[sidx] > 0) == (viewed == 1)) {
+                    p->scene_slot[sidx] = (int32_t)slots.size();
+                    slots.push_back(sidx);
+                }
         uint32_t acc = 0, blk = 0;
-        for (int sidx = 0; sidx < S; ++sidx) {
-            SceneDesc &d = p->sdesc[sidx];
+        for (int slot = 0; slot < S; ++slot) {
+            const int sidx = slots[slot];
+            SceneDesc &d = p->sdesc[slot];
             memset(&d, 0, sizeof(d));
             d.n = (int32_t)scenes[sidx].n;
             d.sh_degree = scenes[sidx].sh_degree;
@@ -556,12 +571,13 @@ int plan_forward_impl(const dpr_scene *scenes, int32_t n_scenes, const dpr_view 
             d.sh = scenes[sidx].sh;
             d.opacity = scenes[sidx].opacity;
             d.radius = scenes[sidx].radius;
-            scene_block_start[sidx] = blk;
+            scene_block_start[slot] = blk;
             blk += (uint32_t)((d.n + 127) / 128);
             acc += count[sidx];
+            if (count[sidx] > 0) p->viewed_blocks = blk;
         }
         for (int v = 0; v < V; ++v) {
-            SceneDesc &d = p->sdesc[views[v].scene];
+            SceneDesc &d = p->sdesc[p->scene_slot[views[v].scene]];
             scene_views[d.view_start + d.view_count++] = (uint32_t)v;
         }
     }
@@ -643,7 +659,7 @@ int plan_forward_impl(const dpr_scene *scenes, int32_t n_scenes, const dpr_view 
     }
     {
         StageScope sc_(p, DPR_STAGE_PROJECT, st);
-        STAGE_TRY(launch_project(tb, p->th, s.sh_degree, (uint32_t)s.point_blocks, rec, keys_alt, rect, scratch,
+        STAGE_TRY(launch_project(tb, p->th, s.sh_degree, (uint32_t)p->viewed_blocks, rec, keys_alt, rect, scratch,
                                  st));
     }
     {
@@ -803,9 +819,10 @@ int dpr_render_backward(dpr_plan *p, const void *ws, size_t ws_bytes, const floa
     }
     p->sdesc_bwd = p->sdesc;
     for (int s = 0; s < S; ++s) {
-        p->sdesc_bwd[s].dxyz = dL_dxyz ? dL_dxyz[s] : nullptr;
-        p->sdesc_bwd[s].dsh = dL_dsh ? dL_dsh[s] : nullptr;
-        p->sdesc_bwd[s].dopacity = dL_dopacity ? dL_dopacity[s] : nullptr;
+        SceneDesc &d = p->sdesc_bwd[p->scene_slot[s]];
+        d.dxyz = dL_dxyz ? dL_dxyz[s] : nullptr;
+        d.dsh = dL_dsh ? dL_dsh[s] : nullptr;
+        d.dopacity = dL_dopacity ? dL_dopacity[s] : nullptr;
     }
     // pointer tables and gradient scene descriptors (adjacent regions: one
     // image), with the counters and the gradient accumulators cleared in the
