@@ -246,7 +246,7 @@ struct StageScope {
 };
 
 // Per-pixel and per-tile state a backward reads: stop index, final (T, I),
-// (T, I) checkpoints every kBwdSeg list positions, and (tile, segment) work
+// (T, I) checkpoints every bwd_seg list positions, and (tile, segment) work
 // items.  Held in the forward workspace in stored mode and in the backward
 // workspace in recompute mode.
 struct BwdState {
@@ -860,6 +860,7 @@ int dpr_render_backward(dpr_plan *p, const void *ws, size_t ws_bytes, const floa
     b.ckpt = a.ckpt;
     b.work = a.work;
     b.queue = counters + 2;
+    b.most_items = work_capacity(p->pairs, p->sz.tiles);
     a.nlast = nullptr;
     a.fin = nullptr;
     a.ckpt = nullptr;

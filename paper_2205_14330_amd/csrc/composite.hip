@@ -135,15 +135,15 @@ static_assert(kFwdChunk % kFwdGroup == 0, "whole groups fit the staged chunk");
 // With backward state requested (a.nlast non-null) the kernel also writes,
 // per pixel, its blend end (one past the list position of the last splat it
 // blended, 0 if none: no later splat changes the pixel) and the final (T, I);
-// at every list position s * kBwdSeg its wave reaches, the (T, I) checkpoint
+// at every list position s * seg its wave reaches, the (T, I) checkpoint
 // of each of the wave's pixels (a pixel that blends past that position keeps
 // its wave walking, so every checkpoint the backward reads is written); and
 // it appends the tile's backward work items (tile, s) for
-// s < ceil(max blend end / kBwdSeg).  Within a group a pixel keeps the
+// s < ceil(max blend end / seg), seg = bwd_seg.  Within a group a pixel keeps the
 // group-relative index of its last blended record (a compile-time constant
 // of the unrolled walk), folded into the chunk's kept-record index after the
 // group; the list position is formed once per chunk.
-static_assert(kBwdSeg % kFwdChunk == 0, "backward segments are whole forward chunks");
+static_assert(kBwdSeg % kFwdChunk == 0 && kBwdSegFew % kFwdChunk == 0, "backward segments are whole forward chunks");
 
 // The 8 bits of a 64-lane mask folded over its 8 groups of 8 lanes: bit c is
 // set if lane 8r + c is set for some r.
@@ -175,6 +175,7 @@ __global__ __launch_bounds__(kFwdThreads) void k_composite(CompositeArgs a) {
     const float t_min = in_vgpr(a.th.t_min);
     const uint32_t cap = in_vgpr(a.th.max_splats > 0 ? a.th.max_splats : 0xFFFFFFFFu);
     if (a.tile_base[a.total_tiles] > a.pair_cap) return;   // the pair lists do not fit the workspace
+    const uint32_t seg = bwd_seg(a.tile_base[a.total_tiles], a.total_tiles);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     // block (or popped) index -> tile: through the longest-first order when there is one
     for (uint32_t idx = blockIdx.x; idx < a.total_tiles;) {
@@ -222,8 +223,8 @@ __global__ __launch_bounds__(kFwdThreads) void k_composite(CompositeArgs a) {
             for (int p = 0; p < PX; ++p) live[p] = T[p] >= t_min && (!COUNT || nblend[p] < cap);
             const uint64_t m0 = __ballot(live[0]), m1 = __ballot(live[1]);
             if ((m0 | m1) == 0ull) break;
-            if (STATE && a.ckpt && base > start && (base - start) % (uint32_t)kBwdSeg == 0) {
-                float4 *dst = a.ckpt + ckpt_slot(start, tile, (base - start) / (uint32_t)kBwdSeg) * kTilePix +
+            if (STATE && a.ckpt && base > start && (base - start) % seg == 0) {
+                float4 *dst = a.ckpt + ckpt_slot(start, tile, (base - start) / seg, seg) * kTilePix +
                               ly * kTile + lx;
 #pragma unroll
                 for (int p = 0; p < PX; ++p) dst[p] = make_float4(T[p], I0[p], I1[p], I2[p]);
@@ -373,12 +374,12 @@ __global__ __launch_bounds__(kFwdThreads) void k_composite(CompositeArgs a) {
             }
         }
         if (STATE) {
-            // the tile's backward work items: one per kBwdSeg positions below its largest blend end
+            // the tile's backward work items: one per seg positions below its largest blend end
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) mymax = max(mymax, (uint32_t)__shfl_xor((int)mymax, d, 64));
             if (lane == 0) s_max[wave] = mymax;
             __syncthreads();
-            const uint32_t nseg = (max(s_max[0], s_max[1]) + (uint32_t)kBwdSeg - 1) / (uint32_t)kBwdSeg;
+            const uint32_t nseg = (max(s_max[0], s_max[1]) + seg - 1) / seg;
             if (tid == 0) s_work = nseg ? atomicAdd(a.counters + 1, nseg) : 0u;
             __syncthreads();
             for (uint32_t i = tid; i < nseg; i += kThreads) a.work[s_work + i] = make_uint2(tile, i);
@@ -446,7 +447,7 @@ __device__ __forceinline__ void flush_slots(const float *s_part, const uint32_t 
 }
 
 // Persistent: each wave pops (tile, segment) work items until the list is
-// exhausted.  Segment s covers list positions [s kBwdSeg, (s + 1) kBwdSeg); a
+// exhausted.  Segment s covers list positions [s seg, (s + 1) seg); a
 // pixel still live after the segment starts from the checkpoint there, any
 // other pixel from its final state.
 __global__ __launch_bounds__(kCompLanes) void k_composite_bwd(BackwardArgs b) {
@@ -461,14 +462,15 @@ __global__ __launch_bounds__(kCompLanes) void k_composite_bwd(BackwardArgs b) {
     const int lane = threadIdx.x;
     float *const my_part = s_part + lane;
     const uint32_t nwork = *b.work_count;
+    const uint32_t seg = bwd_seg(a.tile_base[a.total_tiles], a.total_tiles);
 
     for (uint32_t w = blockIdx.x; w < nwork;) {
         const uint2 item = b.work[w];
         const uint32_t tile = item.x;
-        const uint32_t seg_beg = item.y * (uint32_t)kBwdSeg, seg_end = seg_beg + (uint32_t)kBwdSeg;
+        const uint32_t seg_beg = item.y * seg, seg_end = seg_beg + seg;
         const TileCtx c = tile_ctx(a, tile);
         const ViewDesc &vd = a.views[c.v];
-        const float4 *ck = b.ckpt + ckpt_slot(c.start, tile, item.y + 1) * kTilePix;
+        const float4 *ck = b.ckpt + ckpt_slot(c.start, tile, item.y + 1, seg) * kTilePix;
         // per pixel: T (recovered front-to-back transmittance), dL/dI, and
         // D = dL/dI . B + dL/dT * T_final with B = sum over the blended splats
         // behind of T_k alpha_k c_k, so that dL/dalpha_i = T_i (dL/dI . c_i) - D / (1 - alpha_i).
@@ -678,13 +680,13 @@ __global__ __launch_bounds__(kCompLanes) void k_composite_bwd(BackwardArgs b) {
     }
 }
 
-static uint32_t persistent_grid(uint32_t tiles, uint32_t per_cu) {
+static uint32_t persistent_grid(uint32_t items, uint32_t per_cu) {
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess) {
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
     }
     const uint32_t g = (uint32_t)cus * per_cu;
-    return tiles < g ? tiles : g;
+    return items < g ? items : g;
 }
 
 template <bool COUNT, bool STATE>
@@ -708,11 +710,12 @@ hipError_t launch_composite_fwd(const CompositeArgs &a, bool persistent, hipStre
     return hipGetLastError();
 }
 
-// Persistent, 16 waves per CU; the grid is sized from the tile count (the
-// work-item count is read by the kernel itself).
+// Persistent, 16 waves per CU, or as many as there can be work items (their
+// number is read by the kernel itself; the tile count, which bounded the grid
+// before, left the segments of a small image's tiles to one wave each).
 hipError_t launch_composite_bwd(const BackwardArgs &b, hipStream_t st) {
     if (b.c.total_tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_composite_bwd, dim3(persistent_grid(b.c.total_tiles, 16)), dim3(kCompLanes), 0, st, b);
+    hipLaunchKernelGGL(k_composite_bwd, dim3(persistent_grid((uint32_t)(b.most_items < 0xFFFFFFFFull ? b.most_items : 0xFFFFFFFFull), 16)), dim3(kCompLanes), 0, st, b);
     return hipGetLastError();
 }
 

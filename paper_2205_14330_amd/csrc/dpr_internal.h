@@ -13,7 +13,8 @@ constexpr int kTilePix = kTile * kTile;   // 256 pixels per tile
 constexpr int kChunkItems = 512;          // depth-sorted items per binning chunk
 constexpr int kBandTiles = 8192;          // tiles of one view handled per LDS band
 constexpr int kSegChunks = 16;            // chunks per column-scan segment
-constexpr int kBwdSeg = 256;              // list positions per backward work item
+constexpr int kBwdSeg = 256;              // list positions per backward work item,
+constexpr int kBwdSegFew = 128;           // and where those would be too few
 constexpr int kSortThreads = 256;
 constexpr int kSortItemsPerThread = 8;
 constexpr int kSortTile = kSortThreads * kSortItemsPerThread;   // 2048 keys per sort block
@@ -261,16 +262,37 @@ hipError_t launch_tile_emit(const Tables &tb, uint32_t chunks, const BinRec *bin
                             const uint32_t *tile_base, uint32_t *pairs, uint32_t *zero4, uint32_t pair_cap,
                             hipStream_t st);
 
-// Backward state of a tile list at the list positions s * kBwdSeg (s >= 1):
-// per pixel (T, I) after the first s * kBwdSeg splats, 256 float4 per slot in
-// row-major pixel order.  Slot of (tile t, s) = floor(tile_base[t] / kBwdSeg)
-// + t + s: consecutive tiles' slot ranges never overlap, and every slot is
-// below floor(pairs / kBwdSeg) + tiles + 1.
-__host__ __device__ inline uint64_t ckpt_slot(uint32_t tile_base_t, uint32_t tile, uint32_t s) {
-    return (uint64_t)(tile_base_t / (uint32_t)kBwdSeg) + tile + s;
+// List positions per backward work item of a plan.  A work item is one wave's
+// serial walk, and 16 waves per CU run at once.  Where items of kBwdSeg leave
+// most of them idle, the walk's length is the kernel's duration: shorter items
+// halve it for twice the checkpoints.  pairs / kBwdSeg + tiles bounds the items
+// from above; early termination leaves a third of it, or less.  Backward of 356
+// such items (20k points, 203 x 149): 110 us with 256 positions, 63 with 128;
+// of 5554 (100k, 640 x 480) 149 and 123; of 12.5k 272 and 250; of 21.7k 198 and
+// 195; of 88k (4 x 300k, 800 x 800) 622 and 630.
+constexpr uint64_t kBwdFewItems = 16384;
+__host__ __device__ inline uint32_t bwd_seg(uint64_t pairs, uint64_t tiles) {
+    return pairs / kBwdSeg + tiles < kBwdFewItems ? (uint32_t)kBwdSegFew : (uint32_t)kBwdSeg;
 }
-inline uint64_t ckpt_slots(uint64_t pairs, uint64_t tiles) { return pairs / kBwdSeg + tiles + 2; }
-inline uint64_t work_capacity(uint64_t pairs, uint64_t tiles) { return pairs / kBwdSeg + tiles + 1; }
+
+// Backward state of a tile list at the list positions s * seg (s >= 1):
+// per pixel (T, I) after the first s * seg splats, 256 float4 per slot in
+// row-major pixel order.  Slot of (tile t, s) = floor(tile_base[t] / seg)
+// + t + s: consecutive tiles' slot ranges never overlap, and every slot is
+// below floor(pairs / seg) + tiles + 1.
+__host__ __device__ inline uint64_t ckpt_slot(uint32_t tile_base_t, uint32_t tile, uint32_t s, uint32_t seg) {
+    return (uint64_t)(tile_base_t / seg) + tile + s;
+}
+// A layout for `pairs` pairs also serves every smaller number of them, whose
+// segments may be the shorter ones.
+inline uint64_t bwd_segments(uint64_t pairs, uint64_t tiles) {
+    uint64_t few = 0;                         // the most pairs whose segments are the shorter ones
+    if (tiles < kBwdFewItems) few = (kBwdFewItems - tiles) * kBwdSeg - 1;
+    if (few > pairs) few = pairs;
+    return (pairs / kBwdSeg > few / kBwdSegFew ? pairs / kBwdSeg : few / kBwdSegFew) + tiles;
+}
+inline uint64_t ckpt_slots(uint64_t pairs, uint64_t tiles) { return bwd_segments(pairs, tiles) + 2; }
+inline uint64_t work_capacity(uint64_t pairs, uint64_t tiles) { return bwd_segments(pairs, tiles) + 1; }
 
 struct CompositeArgs {
     const ViewDesc *views;
@@ -317,6 +339,7 @@ struct BackwardArgs {
     const uint32_t *work_count;
     uint32_t *queue;
     float *grad;                    // [items][8] accumulators
+    uint64_t most_items;            // an upper bound of *work_count
 };
 hipError_t launch_composite_bwd(const BackwardArgs &a, hipStream_t st);
 
