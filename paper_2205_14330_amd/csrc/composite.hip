@@ -1,20 +1,20 @@
 // Per-tile front-to-back compositing (Sec. 3.2, Eq. 5-7) and its reverse-mode
 // derivative.
 //
-// Forward: one workgroup of 2 waves per 16x16 tile; wave w owns the 16x8
-// half w, two horizontally adjacent pixels per lane.  Each wave walks the
+// Forward: one workgroup of 4 waves per 16x16 tile, each with an 8x8 quarter
+// of it, a pixel per lane.  Each wave walks the
 // tile's depth-ordered list on its own, in chunks of 128 positions: the splat
 // records are gathered into registers one chunk ahead; at a chunk's start the
 // records that may reach one of the wave's live pixels are kept in LDS, and
 // read back as broadcasts in unrolled groups of 16 (compile-time offsets),
 // each 32-byte record one record ahead of its use.  The blend is branch-free
 // per pixel.  A pixel stops after the first blended
-// splat that leaves T < t_min; a wave leaves the list once its 128 pixels have
+// splat that leaves T < t_min; a wave leaves the list once its 64 pixels have
 // stopped.
 //
 // Backward: one wave per (tile, segment) work item; each lane owns a 2x2
 // pixel quad so that the per-splat reduction is shared by 256 pixels.  A
-// segment is 256 list positions; the forward left at each segment boundary a
+// segment is 256 list positions (128 in small plans); the forward left at each boundary a
 // checkpoint of every pixel's (T, I), so the segments of one long list are
 // processed independently and in parallel (the longest tiles no longer set
 // the kernel's duration).  A segment is walked in reverse from its end (or the
@@ -106,12 +106,12 @@ __device__ __forceinline__ uint32_t pop_tile(uint32_t *queue) {
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-// Two waves per tile: wave w owns rows [8w, 8w + 8), each lane a horizontal
-// pixel pair.  The waves walk the tile's list independently, kFwdChunk list
+// Four waves per tile: wave w owns the 8x8 quarter at (8 (w & 1), 8 (w >> 1)),
+// a pixel per lane.  The waves walk the tile's list independently, kFwdChunk list
 // positions at a time.  Each lane gathers kFwdPerLane records of the next
 // chunk into registers while the current chunk is blended (the ids one chunk
 // further ahead, so the record loads never wait for them).  At the start of a
-// chunk the wave takes the bounding box of its live pixels from two ballots
+// chunk the wave takes the bounding box of its live pixels from a ballot
 // and keeps, in LDS and in list order, only the records that may reach a pixel
 // centre of that box (splat_reaches_box, conservative).  A skipped record
 // cannot blend a live pixel, and a pixel that has stopped blends nothing more,
@@ -120,11 +120,22 @@ __device__ __forceinline__ uint32_t pop_tile(uint32_t *queue) {
 // walked fully unrolled, so every LDS read of a record has a compile-time
 // offset and the walk has no per-record loop control; each record is read one
 // record ahead of its use.  A record that no pixel of the wave blends skips
-// the blend after its exponents.
-constexpr int kFwdPx = 2;                 // pixels per lane
-constexpr int kFwdThreads = 128;
+// the blend after its exponent.
+//
+// Bound by the VALU where the tiles fill the chip, by a wave's instructions per
+// record where they do not.  A quarter of a tile per wave keeps fewer records
+// than a half of it (smaller boxes, earlier ends), and half the instructions
+// per record: against two waves of 16x8 pixels, two pixels per lane, four views
+// of 800x800 (300k points) take 302 us instead of 322, one 88 instead of 102,
+// 640x480 (100k) 69 instead of 98, 128x128 (4096) 18 instead of 30.  Waves of
+// 16x4 pixels take 313 and 92 us for the first two, chunks of 64 positions 310
+// and 91.
+constexpr int kFwdWaves = 4;              // waves per tile, a pixel per lane
+constexpr int kFwdThreads = 64 * kFwdWaves;
 constexpr int kFwdChunk = 128;            // list positions per chunk
 constexpr int kFwdPerLane = kFwdChunk / 64;
+constexpr int kFwdEdge = 8;               // a wave's pixels: kFwdEdge columns and rows
+static_assert(kFwdEdge * kFwdEdge == 64 && kFwdWaves * 64 == kTilePix, "four quarters of a tile");
 constexpr int kFwdGroup = 16;             // kept records per unrolled group
 static_assert(kFwdChunk % kFwdGroup == 0, "whole groups fit the staged chunk");
 
@@ -162,12 +173,12 @@ __device__ __forceinline__ uint32_t fold_columns(uint64_t m) {
 // kernel keeps no blend ends.
 template <bool PERSISTENT, bool COUNT, bool STATE>
 __global__ __launch_bounds__(kFwdThreads) void k_composite(CompositeArgs a) {
-    constexpr int PX = kFwdPx, kThreads = kFwdThreads, kChunk = kFwdChunk, kPer = kFwdPerLane;
+    constexpr int kThreads = kFwdThreads, kChunk = kFwdChunk, kPer = kFwdPerLane;
     // per wave: the kept records of the current chunk (padded to whole groups)
     // and the chunk position of each kept record
-    __shared__ float4 s_r0[2][kChunk], s_r1[2][kChunk];
-    __shared__ uint32_t s_j[2][kChunk];
-    __shared__ uint32_t s_next, s_max[2], s_work;
+    __shared__ float4 s_r0[kFwdWaves][kChunk], s_r1[kFwdWaves][kChunk];
+    __shared__ uint32_t s_j[kFwdWaves][kChunk];
+    __shared__ uint32_t s_next, s_max[kFwdWaves], s_work;
     const float lambda = a.th.lambda;
     const float neg_lambda = in_vgpr(-lambda);
     const float alpha_max = a.th.alpha_max;
@@ -186,22 +197,17 @@ __global__ __launch_bounds__(kFwdThreads) void k_composite(CompositeArgs a) {
         const uint32_t ty = lt / (uint32_t)vd.tiles_x;
         const uint32_t tx = lt - ty * (uint32_t)vd.tiles_x;
         const uint32_t start = a.tile_base[tile], end = a.tile_base[tile + 1];
-        const int lx = 2 * (lane & 7), ly = 8 * wave + (lane >> 3);     // in-tile position of pixel 0
-        const int x0 = (int)(tx * kTile) + lx, y0 = (int)(ty * kTile) + ly;
-        // pixel centres of the wave's first column and row
-        const float cx0 = (float)(tx * kTile) + 0.5f, cy0 = (float)(ty * kTile + 8 * wave) + 0.5f;
-        float ux[PX], uy[PX], T[PX], I0[PX], I1[PX], I2[PX];
-        uint32_t nlast[PX], nblend[PX];
-        int last[PX];                     // index of the last blended kept record of this chunk, or -1
-#pragma unroll
-        for (int p = 0; p < PX; ++p) {
-            const int px = x0 + p, py = y0;
-            ux[p] = (float)px + 0.5f;
-            uy[p] = (float)py + 0.5f;
-            T[p] = (px < vd.width && py < vd.height) ? 1.f : -1.f;
-            I0[p] = I1[p] = I2[p] = 0.f;
-            nlast[p] = 0; nblend[p] = 0; last[p] = -1;
-        }
+        // in-tile position of the wave's first pixel, and of the lane's
+        const int wx = kFwdEdge * (wave & 1), wy = kFwdEdge * (wave >> 1);
+        const int lx = wx + lane % kFwdEdge, ly = wy + lane / kFwdEdge;
+        const int px = (int)(tx * kTile) + lx, py = (int)(ty * kTile) + ly;
+        const bool inside = px < vd.width && py < vd.height;
+        // pixel centres of the lane's pixel, and of the wave's first column and row
+        const float ux = (float)px + 0.5f, uy = (float)py + 0.5f;
+        const float cx0 = (float)((int)(tx * kTile) + wx) + 0.5f, cy0 = (float)((int)(ty * kTile) + wy) + 0.5f;
+        float T = inside ? 1.f : -1.f, I0 = 0.f, I1 = 0.f, I2 = 0.f;
+        uint32_t nlast = 0, nblend = 0;
+        int last = -1;                    // index of the last blended kept record of this chunk, or -1
         // records of the chunk at `base` (registers), ids of the chunk after it
         float4 n0[kPer], n1[kPer];
         uint32_t nid[kPer];
@@ -218,26 +224,16 @@ __global__ __launch_bounds__(kFwdThreads) void k_composite(CompositeArgs a) {
             nid[q] = (k + kChunk < end) ? a.pairs[k + kChunk] : 0u;
         }
         for (uint32_t base = start; base < end; base += kChunk) {
-            bool live[PX];
-#pragma unroll
-            for (int p = 0; p < PX; ++p) live[p] = T[p] >= t_min && (!COUNT || nblend[p] < cap);
-            const uint64_t m0 = __ballot(live[0]), m1 = __ballot(live[1]);
-            if ((m0 | m1) == 0ull) break;
-            if (STATE && a.ckpt && base > start && (base - start) % seg == 0) {
-                float4 *dst = a.ckpt + ckpt_slot(start, tile, (base - start) / seg, seg) * kTilePix +
-                              ly * kTile + lx;
-#pragma unroll
-                for (int p = 0; p < PX; ++p) dst[p] = make_float4(T[p], I0[p], I1[p], I2[p]);
-            }
+            const uint64_t m = __ballot(T >= t_min && (!COUNT || nblend < cap));
+            if (m == 0ull) break;
+            if (STATE && a.ckpt && base > start && (base - start) % seg == 0)
+                a.ckpt[ckpt_slot(start, tile, (base - start) / seg, seg) * kTilePix + ly * kTile + lx] =
+                    make_float4(T, I0, I1, I2);
             // the live pixels' box: rows from the first and last live lane
-            // (row = lane / 8), columns from the folded masks of the even
-            // (pixel 0) and odd (pixel 1) columns
-            const uint64_t m = m0 | m1;
-            const int r_lo = __builtin_ctzll(m) >> 3, r_hi = (63 - __builtin_clzll(m)) >> 3;
-            const uint32_t c0 = fold_columns(m0), c1 = fold_columns(m1);
-            int x_lo = 2 * kTile, x_hi = -1;
-            if (c0) { x_lo = 2 * __builtin_ctz(c0); x_hi = 2 * (31 - __builtin_clz(c0)); }
-            if (c1) { x_lo = min(x_lo, 2 * __builtin_ctz(c1) + 1); x_hi = max(x_hi, 2 * (31 - __builtin_clz(c1)) + 1); }
+            // (row = lane / 8), columns from the folded mask
+            const int r_lo = __builtin_ctzll(m) / kFwdEdge, r_hi = (63 - __builtin_clzll(m)) / kFwdEdge;
+            const uint32_t cm = fold_columns(m);
+            const int x_lo = __builtin_ctz(cm), x_hi = 31 - __builtin_clz(cm);
             const float bx0 = cx0 + (float)x_lo, bx1 = cx0 + (float)x_hi;
             const float by0 = cy0 + (float)r_lo, by1 = cy0 + (float)r_hi;
             // keep the records that may reach the box, in list order
@@ -286,49 +282,29 @@ __global__ __launch_bounds__(kFwdThreads) void k_composite(CompositeArgs a) {
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             for (int j0 = 0; j0 < kept; j0 += kFwdGroup) {
-                if (j0 > 0) {
-                    bool any_live = false;
-#pragma unroll
-                    for (int p = 0; p < PX; ++p) any_live = any_live || (T[p] >= t_min && (!COUNT || nblend[p] < cap));
-                    if (__ballot(any_live) == 0ull) break;
-                }
-                int lrel[PX];
-#pragma unroll
-                for (int p = 0; p < PX; ++p) lrel[p] = -1;
+                if (j0 > 0 && __ballot(T >= t_min && (!COUNT || nblend < cap)) == 0ull) break;
+                int lrel = -1;
                 auto blend = [&](const float4 &r0, const float4 &r1, int jr) {
                     SplatRec s;
                     s.px = r0.x; s.py = r0.y; s.a = r0.z; s.b = r0.w;
                     s.w = r1.x;
                     s.cr = r1.y; s.cg = r1.z; s.cb = r1.w;
-                    float alpha[PX], e[PX];
-                    bool hit[PX];
-                    bool any = false;
-#pragma unroll
-                    for (int p = 0; p < PX; ++p) {
-                        float dx, dy;
-                        e[p] = splat_exponent(s, ux[p], uy[p], dx, dy);
-                        hit[p] = (T[p] >= t_min) & (!COUNT || nblend[p] < cap) & (e[p] >= neg_lambda);
-                        any = any || hit[p];
-                    }
-                    if (__ballot(any) == 0ull) return;
-#pragma unroll
-                    for (int p = 0; p < PX; ++p) alpha[p] = hit[p] ? __builtin_amdgcn_exp2f(e[p]) : 0.f;
+                    float dx, dy;
+                    const float e = splat_exponent(s, ux, uy, dx, dy);
+                    const bool hit = (T >= t_min) & (!COUNT || nblend < cap) & (e >= neg_lambda);
+                    if (__ballot(hit) == 0ull) return;
+                    float alpha = hit ? __builtin_amdgcn_exp2f(e) : 0.f;
                     if (__builtin_expect(chunk_clamp, 0)) {
                         const float am = in_vgpr(alpha_max);
-#pragma unroll
-                        for (int p = 0; p < PX; ++p)
-                            if (alpha[p] > am) alpha[p] = am;
+                        if (alpha > am) alpha = am;
                     }
-#pragma unroll
-                    for (int p = 0; p < PX; ++p) {
-                        const float Ta = T[p] * alpha[p];
-                        I0[p] = fmaf(Ta, s.cr, I0[p]);
-                        I1[p] = fmaf(Ta, s.cg, I1[p]);
-                        I2[p] = fmaf(Ta, s.cb, I2[p]);
-                        if (COUNT) nblend[p] += hit[p] ? 1u : 0u;
-                        T[p] = T[p] - Ta;
-                        if (STATE && hit[p]) lrel[p] = jr;
-                    }
+                    const float Ta = T * alpha;
+                    I0 = fmaf(Ta, s.cr, I0);
+                    I1 = fmaf(Ta, s.cg, I1);
+                    I2 = fmaf(Ta, s.cb, I2);
+                    if (COUNT) nblend += hit ? 1u : 0u;
+                    T = T - Ta;
+                    if (STATE && hit) lrel = jr;
                 };
                 const float4 *q0 = s_r0[wave] + j0, *q1 = s_r1[wave] + j0;
                 float4 a0 = q0[0], a1 = q1[0];
@@ -339,47 +315,42 @@ __global__ __launch_bounds__(kFwdThreads) void k_composite(CompositeArgs a) {
                     blend(a0, a1, j);
                     a0 = c0; a1 = c1;
                 }
-#pragma unroll
-                for (int p = 0; p < PX; ++p)
-                    if (STATE && lrel[p] >= 0) last[p] = j0 + lrel[p];
+                if (STATE && lrel >= 0) last = j0 + lrel;
             }
-#pragma unroll
-            for (int p = 0; p < PX; ++p)
-                if (STATE && last[p] >= 0) {
-                    nlast[p] = base - start + s_j[wave][last[p]] + 1u;
-                    last[p] = -1;
-                }
+            if (STATE && last >= 0) {
+                nlast = base - start + s_j[wave][last] + 1u;
+                last = -1;
+            }
             // this chunk's kept records are read before the next chunk's are written
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        uint32_t mymax = 0;
-#pragma unroll
-        for (int p = 0; p < PX; ++p) {
-            const int px = x0 + p, py = y0;
-            if (px >= vd.width || py >= vd.height) continue;
+        if (inside) {
             const uint64_t lpix = (uint64_t)py * (uint64_t)vd.width + (uint64_t)px;
             const uint64_t pix = vd.pix_off + lpix;
             if (a.write_views) {
                 float *img = vd.image + 3 * lpix;
-                img[0] = I0[p]; img[1] = I1[p]; img[2] = I2[p];
-                if (vd.trans) vd.trans[lpix] = T[p];
-                if (COUNT && a.stats) a.stats[pix] = nblend[p];
+                img[0] = I0; img[1] = I1; img[2] = I2;
+                if (vd.trans) vd.trans[lpix] = T;
+                if (COUNT && a.stats) a.stats[pix] = nblend;
             }
             if (STATE) {
-                a.nlast[pix] = nlast[p];
-                a.fin[pix] = make_float4(T[p], I0[p], I1[p], I2[p]);
-                mymax = max(mymax, nlast[p]);
+                a.nlast[pix] = nlast;
+                a.fin[pix] = make_float4(T, I0, I1, I2);
             }
         }
         if (STATE) {
+            uint32_t mymax = inside ? nlast : 0u;
             // the tile's backward work items: one per seg positions below its largest blend end
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) mymax = max(mymax, (uint32_t)__shfl_xor((int)mymax, d, 64));
             if (lane == 0) s_max[wave] = mymax;
             __syncthreads();
-            const uint32_t nseg = (max(s_max[0], s_max[1]) + seg - 1) / seg;
+            uint32_t tmax = s_max[0];
+#pragma unroll
+            for (int w = 1; w < kFwdWaves; ++w) tmax = max(tmax, s_max[w]);
+            const uint32_t nseg = (tmax + seg - 1) / seg;
             if (tid == 0) s_work = nseg ? atomicAdd(a.counters + 1, nseg) : 0u;
             __syncthreads();
             for (uint32_t i = tid; i < nseg; i += kThreads) a.work[s_work + i] = make_uint2(tile, i);
