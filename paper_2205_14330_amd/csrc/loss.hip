@@ -8,9 +8,14 @@
 //
 // An image is a flat array of 3 W H floats; its horizontal neighbours are 3
 // floats away and its vertical ones 3 W.  Each thread owns 4 consecutive
-// floats and reads them, their horizontal neighbourhood, the target and (when
-// 3 W is a multiple of 4) the rows above and below as aligned 16-byte loads;
-// the gradient is written as one 16-byte store.  The loss terms of a float are
+// floats and reads them, their horizontal neighbourhood, the target and the
+// rows above and below as 16-byte loads; the gradient is written as one
+// 16-byte store.  The loads and the store assume 4-byte alignment only, so one
+// path serves every width and base address: a row is 3 W floats, so its
+// neighbours above and below are rarely 16-byte aligned, and reading those
+// float by float, under a branch each, made four 797x803 images take 49 us
+// instead of 27.  A thread's pixel follows from its block's (one 64-bit
+// division, uniform over the block) by 32-bit divisions.  The loss terms of a float are
 // its squared difference and its differences to the right and lower
 // neighbours; a block sums them in FP32, and a second kernel adds each
 // image's block sums in FP64 in a fixed order, so the result does not depend
@@ -33,11 +38,10 @@ struct LossBatch {
 
 __device__ __forceinline__ float sgn(float d) { return (float)(d > 0.f) - (float)(d < 0.f); }
 
-__device__ __forceinline__ float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+// Four floats at any float's address (global 16-byte accesses need 4-byte alignment).
+typedef float F4 __attribute__((ext_vector_type(4), aligned(4)));
 
-__device__ __forceinline__ float at(const float4 &v, int k) {
-    return k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w;
-}
+__device__ __forceinline__ F4 ld4(const float *p) { return *reinterpret_cast<const F4 *>(p); }
 
 __global__ __launch_bounds__(kLossThreads) void k_loss(LossBatch bt) {
     __shared__ float s_sum[kLossThreads / 64];
@@ -47,22 +51,24 @@ __global__ __launch_bounds__(kLossThreads) void k_loss(LossBatch bt) {
     const int W = im.width, H = im.height;
     const int64_t nf = 3ll * W * H;
     const int64_t row = 3ll * W;
-    const int64_t i = ((int64_t)(blockIdx.x - bt.block_start[v]) * kLossThreads + threadIdx.x) * 4;
+    const int64_t i0 = (int64_t)(blockIdx.x - bt.block_start[v]) * kLossFloats;     // the block's first float
+    const int64_t i = i0 + 4 * threadIdx.x;
     const float lambda = bt.lambda;
     float acc = 0.f;
     if (i < nf) {
         const float *R = im.render, *T = im.target;
-        const bool vec = i + 4 <= nf && (((uintptr_t)R | (uintptr_t)T | (uintptr_t)im.grad) & 15) == 0;
-        const bool vrow = vec && (row & 3) == 0;
-        // first float's pixel and channel; the 4 floats span at most 2 pixels
-        const int64_t p0 = i / 3;
-        const int c0 = (int)(i - 3 * p0);
-        const int y0 = (int)(p0 / W), x0 = (int)(p0 - (int64_t)y0 * W);
-        float4 r, t, up, dn, lf, rt;
+        const bool vec = i + 4 <= nf;
+        // first float's pixel and channel, from the block's; the 4 floats span at most 2 pixels
+        const int64_t pb = i0 / 3;
+        const int yb = (int)(pb / W), xb = (int)(pb - (int64_t)yb * W);
+        const uint32_t f = (uint32_t)(i0 - 3 * pb) + 4 * threadIdx.x;
+        const uint32_t xd = (uint32_t)xb + f / 3;
+        const int c0 = (int)(f % 3);
+        const int y0 = yb + (int)(xd / (uint32_t)W), x0 = (int)(xd % (uint32_t)W);
+        F4 r = 0.f, t = 0.f, up = 0.f, dn = 0.f, lf = 0.f, rt = 0.f;
         if (vec) {
             r = ld4(R + i);
             t = ld4(T + i);
-            lf = rt = up = dn = make_float4(0.f, 0.f, 0.f, 0.f);
             if (lambda != 0.f) {                      // the neighbours enter only the TV term
                 if (i >= 4) lf = ld4(R + i - 4);
                 if (i + 8 <= nf) {
@@ -73,9 +79,19 @@ __global__ __launch_bounds__(kLossThreads) void k_loss(LossBatch bt) {
                     rt.z = i + 6 < nf ? R[i + 6] : 0.f;
                     rt.w = 0.f;                       // i + 7: only e + 3 <= i + 6 is ever read
                 }
-                if (vrow) {
-                    if (i >= row) up = ld4(R + i - row);
-                    if (i + row + 4 <= nf) dn = ld4(R + i + row);
+                if (i >= row) {
+                    up = ld4(R + i - row);
+                } else if (i + 4 > row) {             // the second row begins inside the group
+#pragma unroll
+                    for (int k = 1; k < 4; ++k)
+                        if (i + k >= row) up[k] = R[i + k - row];
+                }
+                if (i + row + 4 <= nf) {
+                    dn = ld4(R + i + row);
+                } else if (i + row < nf) {            // the last row ends inside the group
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+                        if (i + k + row < nf) dn[k] = R[i + k + row];
                 }
             }
         }
@@ -90,17 +106,14 @@ __global__ __launch_bounds__(kLossThreads) void k_loss(LossBatch bt) {
             if (x == W) { x = 0; ++y; }
             float Rv, Tv, Rl = 0.f, Rr = 0.f, Ru = 0.f, Rd = 0.f;
             if (vec) {
-                Rv = at(r, k);
-                Tv = at(t, k);
+                Rv = r[k];
+                Tv = t[k];
                 // e - 3 is float k - 3 of the group: k >= 3 in r, else float k + 1 of lf
-                Rl = k >= 3 ? at(r, k - 3) : at(lf, k + 1);
+                Rl = k >= 3 ? r[0] : lf[(k + 1) & 3];
                 // e + 3: float k + 3 of the group: k == 0 in r, else float k - 1 of rt
-                Rr = k == 0 ? at(r, 3) : at(rt, k - 1);
-                if (vrow) { Ru = at(up, k); Rd = at(dn, k); }
-                else if (lambda != 0.f) {
-                    if (y > 0) Ru = R[e - row];
-                    if (y + 1 < H) Rd = R[e + row];
-                }
+                Rr = k == 0 ? r[3] : rt[(k - 1) & 3];
+                Ru = up[k];
+                Rd = dn[k];
             } else {
                 Rv = R[e];
                 Tv = T[e];
@@ -127,7 +140,8 @@ __global__ __launch_bounds__(kLossThreads) void k_loss(LossBatch bt) {
             g[k] = gr;
         }
         if (vec) {
-            *reinterpret_cast<float4 *>(im.grad + i) = make_float4(g[0], g[1], g[2], g[3]);
+            F4 gv = {g[0], g[1], g[2], g[3]};
+            *reinterpret_cast<F4 *>(im.grad + i) = gv;
         } else {
             for (int k = 0; k < 4 && i + k < nf; ++k) im.grad[i + k] = g[k];
         }
