@@ -309,6 +309,10 @@ class RenderFn(torch.autograd.Function):
         plan = Plan([scene], [(0, c) for c in cameras], params, images=list(img.unbind(0)),
                     trans=list(tr.unbind(0)))
         plan.forward()
+        # The plan's lists are views of the outputs, whose graph node holds the plan: kept, they close a reference
+        # cycle through the views' bases that Python cannot see, and every render's buffers stay allocated.  The
+        # backward reads neither images nor transmittances.
+        plan.images, plan.trans = [], []
         ctx.plan = plan
         ctx.save_for_backward(tr)
         return img, tr
@@ -319,7 +323,7 @@ class RenderFn(torch.autograd.Function):
         plan: Plan = ctx.plan
         V = g_img.shape[0] if g_img is not None else tr.shape[0]
         if g_img is None:
-            g_img = torch.zeros((V,) + tuple(plan.images[0].shape), device=tr.device)
+            g_img = torch.zeros(tuple(tr.shape) + (3,), device=tr.device)
         g_img = g_img.contiguous().float()
         gi = list(g_img.unbind(0))
         gt = None
