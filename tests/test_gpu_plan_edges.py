@@ -1,0 +1,96 @@
+"""Plans at the edges of their rules: scenes without views between scenes with
+some, and tile lists that end around a backward segment of 128 positions (small
+plans) or 256 (plans of many tiles)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+from _gpu_util import compare_grads, compare_images, gpu_plan, oparams, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dpr():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2205_14330_amd as d
+    return d
+
+
+@pytest.mark.parametrize("order", [(1, 3), (4, 1, 1), (0, 5, 2), (5,)])
+def test_scenes_without_views(dpr, order):
+    import torch
+    scenes = [workloads.small_scene(200 + i, 300 * i + 37, extent=0.6) for i in range(6)]
+    rng = np.random.default_rng(len(order))
+    cams = [workloads.random_sphere_camera(rng, 40, 33) for _ in order]
+    params = dpr.RenderParams()
+    plan = gpu_plan(scenes, list(zip(order, cams)), params)
+    gI = [rng.standard_normal((33, 40, 3)).astype(np.float32) for _ in order]
+    got = plan.backward([torch.from_numpy(g).cuda() for g in gI])
+    torch.cuda.synchronize()
+    for v, (si, cam) in enumerate(zip(order, cams)):
+        compare_images(to_np(plan.images[v]), to_np(plan.trans[v]), oracle.render(scenes[si], cam, oparams(params)),
+                       label=f"view {v}")
+    for si, sc in enumerate(scenes):
+        mine = [v for v, s in enumerate(order) if s == si]
+        if not mine:
+            assert all(not to_np(t).any() for t in got[si])
+            continue
+        ref = oracle.backward(sc, [cams[v] for v in mine], [gI[v] for v in mine], None, params=oparams(params))
+        for t, r, name in zip(got[si], (ref.xyz, ref.sh, ref.opacity), ("dxyz", "dsh", "dopacity")):
+            compare_grads(to_np(t), r, f"scene {si} {name}")
+
+
+def _window_gradients(dpr, n, c, size, mode):
+    """n splats on the same few pixels, none opaque enough to end a list early, and weights on the pixels around
+    them only; the principal point is (c, c) whatever the image's size."""
+    import torch
+    rng = np.random.default_rng(n)
+    f = 500.0
+    z = rng.uniform(2.0, 3.0, n)
+    px = 56 + rng.uniform(-3, 3, (n, 2))
+    xyz = np.concatenate([(px - c) * z[:, None] / f, z[:, None]], 1).astype(np.float32)
+    sc = workloads.Scene(xyz, (0.3 * rng.standard_normal((n, 4, 3))).astype(np.float32),
+                         rng.uniform(0.01, 0.02, n).astype(np.float32), np.full(n, 0.012, np.float32))
+    cam = workloads.Camera(np.eye(3), np.zeros(3), f, f, c, c, size, size)
+    params = dpr.RenderParams(bwd_mode=mode)
+    win = np.zeros((size, size), bool)
+    win[40:72, 40:72] = True
+    pix = np.flatnonzero(win.reshape(-1))
+    gI, gT = np.zeros((size, size, 3), np.float32), np.zeros((size, size), np.float32)
+    gI[win] = rng.standard_normal((len(pix), 3))
+    gT[win] = rng.standard_normal(len(pix))
+    plan = gpu_plan([sc], [(0, cam)], params)
+    out = plan.backward([torch.from_numpy(gI).cuda()], [torch.from_numpy(gT).cuda()])[0]
+    torch.cuda.synchronize()
+    return sc, cam, params, pix, gI, gT, plan, [to_np(t) for t in out]
+
+
+NAMES = ("dxyz", "dsh", "dopacity")
+
+
+@pytest.mark.parametrize("mode", ["stored", "recompute"])
+@pytest.mark.parametrize("n", [1, 127, 128, 129, 255, 256, 257, 385])
+def test_lists_around_a_short_segment(dpr, n, mode):
+    sc, cam, params, pix, gI, gT, plan, got = _window_gradients(dpr, n, 48.0, 96, mode)
+    compare_images(to_np(plan.images[0]), to_np(plan.trans[0]), oracle.render(sc, cam, oparams(params), pixels=pix),
+                   pixels=pix, label="window")
+    ref = oracle.backward(sc, [cam], [gI.reshape(-1, 3)[pix]], [gT.reshape(-1)[pix]], params=oparams(params),
+                          pixels=[pix])
+    for t, r, name in zip(got, (ref.xyz, ref.sh, ref.opacity), NAMES):
+        compare_grads(t, r, f"n {n} {mode} {name}")
+
+
+@pytest.mark.parametrize("mode", ["stored", "recompute"])
+@pytest.mark.parametrize("n", [1, 127, 128, 129, 255, 256, 257, 385])
+def test_segment_lengths_agree(dpr, n, mode):
+    """The same splats and pixels in an image of 36 tiles (segments of 128 positions) and of 16641 (256)."""
+    few = _window_gradients(dpr, n, 48.0, 96, mode)[-1]
+    many = _window_gradients(dpr, n, 48.0, 2064, mode)[-1]
+    for a, b, name in zip(few, many, NAMES):
+        # FP32 sums over the same pixels from checkpoints at other positions; as stored against recomputed state
+        assert np.abs(a - b).max() <= 1e-5 * np.abs(a).max(), name
