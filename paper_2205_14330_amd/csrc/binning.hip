@@ -320,16 +320,27 @@ hipError_t launch_tile_colscan(const Tables &tb, uint32_t *cnt, uint32_t *segs, 
 // view's tiles are taken in bands: a rectangle of whole tile rows (as many as
 // fit kEmitBand tiles), or of a part of one row on views wider than kEmitBand
 // tiles.  Per band:
-//   mark : each thread takes items (i = tid, tid + kEmitThreads, ...) and sets
-//          bit i of the bitmap of every tile of the band it touches, and the
-//          bit of that bitmap word in the tile's word summary (LDS atomic OR:
-//          the order of the updates does not matter, a bit's place is the
-//          item's place in the chunk);
-//   write: each thread takes a tile and walks the non-empty words of its
-//          bitmap in bit order, so the tile's segment comes out in item order,
-//          stored by one lane in consecutive instructions at
-//          tile_base[t] + cnt[chunk][t] (loaded while the band is marked); it
-//          clears the words it reads, so the next band starts clear.
+//   mark : sets bit i of the bitmap of every tile of the band that item i
+//          touches, and the bit of that bitmap word in the tile's word summary
+//          (LDS atomic OR: the order of the updates does not matter, a bit's
+//          place is the item's place in the chunk).  A wave holds 64 items.
+//          Where at most kEmitFewActive of them reach the band, kEmitRows lanes
+//          take the rows of each that does; where more do (a view of one or
+//          two bands), a lane takes its item;
+//   write: a tile has 2^log_s threads, as many as the band leaves it, each with
+//          a part of its bitmap; a thread walks its non-empty words in bit
+//          order, so the tile's segment comes out in item order, at
+//          tile_base[t] + cnt[chunk][t] (loaded while the band is marked) plus
+//          the bits of the parts before; it clears the words it reads, so the
+//          next band starts clear.  Ids are stored up to four at a time.
+// Bound by instructions and by the requests of the scattered stores.  Marking
+// an item per lane left most lanes of a wave idle in every band, and a store
+// per id was one L2 request each: 4 x 300k splats at 800x800 (20.0M pairs) 131
+// us, with four ids per store 115, with lanes per row as well 104; 8 x 200k at
+// 1024x768 283, 241 and 203; 50k at 1920x1080 129, 136 and 99.  Two lanes per
+// item 106, 205 and 107; eight 112, 218 and 113.  With up to 64 of 64 items
+// active (20k at 203x149) lanes per row and one thread per tile took 16.4 us
+// against 12.4; a lane per item and the split tiles take 12.2.
 // Every (item, tile) decision is splat_touches_tile, as in the count, so each
 // segment has exactly the length the count reserved.
 // Block b runs on XCD b % 8 (round-robin dispatch).  The emission maps the
@@ -352,9 +363,16 @@ __device__ __forceinline__ uint32_t emit_chunk_of_block(uint32_t b, uint32_t tot
 constexpr int kEmitThreads = 512;
 constexpr int kEmitBand = 512;                 // tiles per band (at most)
 constexpr int kEmitWords = kChunkItems / 32;   // bitmap words per tile
-constexpr int kEmitTilesPerThread = (kEmitBand + kEmitThreads - 1) / kEmitThreads;
+constexpr uint32_t kEmitRows = 4;              // lanes per item in the mark phase
+constexpr uint32_t kEmitFewActive = 32;        // active items of a wave up to which they get kEmitRows lanes each
+constexpr uint32_t kEmitMaxLogSplit = 4;       // a tile's words over up to 16 threads
 static_assert(kChunkItems % 32 == 0 && kEmitWords <= 32, "whole bitmap words, one summary word");
-static_assert(kEmitThreads == kChunkItems, "one item per emission thread");
+static_assert(kEmitThreads == kChunkItems && kEmitThreads >= kEmitBand, "one item, and one tile, per emission thread");
+static_assert(kEmitWords >> kEmitMaxLogSplit >= 1, "whole words per thread of a tile");
+
+// Item ids at any id's address (global accesses of 8 and 16 bytes need 4-byte alignment).
+typedef uint32_t Id2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t Id4 __attribute__((ext_vector_type(4), aligned(4)));
 
 __global__ __launch_bounds__(kEmitThreads) void k_tile_emit(Tables tb, const BinRec *bin, const uint32_t *pre,
                                                              const uint32_t *tile_base, uint32_t *pairs,
@@ -364,9 +382,11 @@ __global__ __launch_bounds__(kEmitThreads) void k_tile_emit(Tables tb, const Bin
     __shared__ uint32_t s_bits[kEmitWords * kEmitBand];
     __shared__ uint32_t s_sum[kEmitBand];
     __shared__ uint32_t s_g[kChunkItems];
+    __shared__ uint8_t s_act[kEmitThreads / 64][64];
     if (tile_base[tb.total_tiles] > pair_cap) return;     // the pair lists do not fit the workspace
     const ChunkInfo ci = chunk_info(tb, emit_chunk_of_block(blockIdx.x, gridDim.x));
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint64_t below = (1ull << lane) - 1ull;
     const uint32_t n = ci.end - ci.beg;
     if (blockIdx.x == 0 && tid < 4u) zero4[tid] = 0u;
     // thread i holds item i of the chunk (its binning record, read contiguously)
@@ -395,52 +415,108 @@ __global__ __launch_bounds__(kEmitThreads) void k_tile_emit(Tables tb, const Bin
             const uint32_t r1 = min(r0 + bh, TY), c1 = min(c0 + bw, TX);
             const uint32_t bwid = c1 - c0, nt = bwid * (r1 - r0);
             // the band's segment starts, in flight while the band is marked
-            uint32_t pos[kEmitTilesPerThread];
-#pragma unroll
-            for (int q = 0; q < kEmitTilesPerThread; ++q) {
-                const uint32_t lt = tid + (uint32_t)q * kEmitThreads;
-                pos[q] = 0;
-                if (lt < nt) {
-                    const uint32_t rr = lt / bwid, t = (r0 + rr) * TX + c0 + (lt - rr * bwid);
-                    pos[q] = tile_base[ci.tile_off + t] + pre[ci.row + t];
-                }
+            uint32_t log_s = 0;           // 2^log_s threads per tile
+            while (log_s < kEmitMaxLogSplit && nt << (log_s + 1u) <= (uint32_t)kEmitThreads) ++log_s;
+            const uint32_t lt = tid >> log_s, rr = lt / bwid, b = rr * bw + (lt - rr * bwid);
+            uint32_t p = 0;
+            if (lt < nt) {
+                const uint32_t t = (r0 + rr) * TX + c0 + (lt - rr * bwid);
+                p = tile_base[ci.tile_off + t] + pre[ci.row + t];
             }
             __syncthreads();              // the bitmaps are clear; the staged items are published
             {
                 // an item outside the chunk has an empty rectangle
                 const uint32_t x0 = max(ra.x & 0xFFFFu, c0), y0 = max(ra.x >> 16, r0);
                 const uint32_t x1 = min(ra.y & 0xFFFFu, c1), y1 = min(ra.y >> 16, r1);
-                const uint32_t bit = 1u << (i & 31u), word = i >> 5, wbit = 1u << word;
-                uint32_t *const bits = s_bits + word * (uint32_t)kEmitBand;
-                for (uint32_t ty = y0; ty < y1; ++ty) {
-                    const uint32_t rowb = (ty - r0) * bw - c0;
-                    for (uint32_t cx = x0; cx < x1; ++cx) {
-                        if (splat_touches_tile(spx, spy, sa, sb, thr, cx, ty)) {
-                            atomicOr(&bits[rowb + cx], bit);
-                            atomicOr(&s_sum[rowb + cx], wbit);
+                const bool act = x0 < x1 && y0 < y1;
+                const uint64_t acts = __ballot(act);
+                const uint32_t na = (uint32_t)__popcll(acts);
+                if (na > kEmitFewActive) {
+                    for (uint32_t ty = y0; act && ty < y1; ++ty) {
+                        const uint32_t rowb = (ty - r0) * bw - c0;
+                        for (uint32_t cx = x0; cx < x1; ++cx) {
+                            if (splat_touches_tile(spx, spy, sa, sb, thr, cx, ty)) {
+                                atomicOr(&s_bits[(i >> 5) * (uint32_t)kEmitBand + rowb + cx], 1u << (i & 31u));
+                                atomicOr(&s_sum[rowb + cx], 1u << (i >> 5));
+                            }
+                        }
+                    }
+                } else {
+                    const uint32_t xs = x0 | x1 << 16, ys = y0 | y1 << 16;
+                    if (act) s_act[wave][__popcll(acts & below)] = (uint8_t)lane;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    for (uint32_t k = 0; k < na; k += 64u / kEmitRows) {
+                        const uint32_t at = k + lane / kEmitRows;
+                        const int src = at < na ? (int)s_act[wave][at] : 0;
+                        const uint32_t ix = __shfl(xs, src, 64), iy = __shfl(ys, src, 64);
+                        const float ipx = __shfl(spx, src, 64), ipy = __shfl(spy, src, 64);
+                        const float ia = __shfl(sa, src, 64), ib = __shfl(sb, src, 64), it = __shfl(thr, src, 64);
+                        if (at < na) {
+                            const uint32_t bit = 1u << (src & 31), word = 2u * wave + ((uint32_t)src >> 5);
+                            uint32_t *const bits = s_bits + word * (uint32_t)kEmitBand;
+                            for (uint32_t ty = (iy & 0xFFFFu) + lane % kEmitRows; ty < iy >> 16; ty += kEmitRows) {
+                                const uint32_t rowb = (ty - r0) * bw - c0;
+                                for (uint32_t cx = ix & 0xFFFFu; cx < ix >> 16; ++cx) {
+                                    if (splat_touches_tile(ipx, ipy, ia, ib, it, cx, ty)) {
+                                        atomicOr(&bits[rowb + cx], bit);
+                                        atomicOr(&s_sum[rowb + cx], 1u << word);
+                                    }
+                                }
+                            }
                         }
                     }
                 }
             }
             __syncthreads();
+            uint32_t words = 0;
+            if (lt < nt) {
+                const uint32_t part = tid & ((1u << log_s) - 1u), len = (uint32_t)kEmitWords >> log_s;
+                words = s_sum[b] & (((1u << len) - 1u) << (part * len));
+            }
+            if (log_s) {                  // the items of the tile's earlier parts come first
+                uint32_t c = 0;
+                for (uint32_t ws = words; ws; ws &= ws - 1u)
+                    c += (uint32_t)__popc(s_bits[(uint32_t)__builtin_ctz(ws) * (uint32_t)kEmitBand + b]);
+                uint32_t before = c;
+                for (uint32_t d = 1; d < 1u << log_s; d <<= 1) {
+                    const uint32_t y = __shfl_up(before, d, 64);
+                    if ((tid & ((1u << log_s) - 1u)) >= d) before += y;
+                }
+                p += before - c;
+            }
+            if (lt < nt) {
+                s_sum[b] = 0u;            // its threads, of one wave, have all read it
+                uint32_t m = 0, w = 0;
+                while (m | words) {
+                    // the next four items (fewer at the end of the segment), stored together
+                    uint32_t id[4], c = 0;
 #pragma unroll
-            for (int q = 0; q < kEmitTilesPerThread; ++q) {
-                const uint32_t lt = tid + (uint32_t)q * kEmitThreads;
-                if (lt >= nt) continue;
-                const uint32_t rr = lt / bwid, b = rr * bw + (lt - rr * bwid);
-                uint32_t p = pos[q];
-                uint32_t words = s_sum[b];
-                s_sum[b] = 0u;
-                while (words) {
-                    const uint32_t w = (uint32_t)__builtin_ctz(words);
-                    words &= words - 1u;
-                    uint32_t m = s_bits[w * (uint32_t)kEmitBand + b];
-                    s_bits[w * (uint32_t)kEmitBand + b] = 0u;
-                    while (m) {
-                        const uint32_t k = (uint32_t)__builtin_ctz(m);
+                    for (int u = 0; u < 4; ++u) {
+                        if (m == 0u && words != 0u) {
+                            w = (uint32_t)__builtin_ctz(words);
+                            words &= words - 1u;
+                            m = s_bits[w * (uint32_t)kEmitBand + b];
+                            s_bits[w * (uint32_t)kEmitBand + b] = 0u;
+                        }
+                        id[u] = w * 32u + (uint32_t)__builtin_ctz(m | 0x80000000u);
+                        c += m != 0u ? 1u : 0u;
                         m &= m - 1u;
-                        pairs[p++] = s_g[w * 32u + k];
                     }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) id[u] = s_g[id[u]];
+                    if (c == 4u) {
+                        const Id4 v = {id[0], id[1], id[2], id[3]};
+                        *reinterpret_cast<Id4 *>(pairs + p) = v;
+                    } else {
+                        if (c & 2u) {
+                            const Id2 v = {id[0], id[1]};
+                            *reinterpret_cast<Id2 *>(pairs + p) = v;
+                        }
+                        if (c & 1u) pairs[p + (c & 2u)] = c == 1u ? id[0] : id[2];
+                    }
+                    p += c;
                 }
             }
             __syncthreads();              // the bitmaps are read before the next band clears them
