@@ -56,6 +56,9 @@ struct HullArgs {
 };
 
 // Ten rounds of Philox4x32 (multipliers and key increments of the SC 2011 paper).
+// Both halves of a product come from one 64-bit multiply (a quarter-rate
+// instruction either way): sampling 2^24 candidates 259 us, with a multiply for
+// each half 262.
 __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
@@ -63,13 +66,11 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
             k0 += 0x9E3779B9u;
             k1 += 0xBB67AE85u;
         }
-        const uint32_t p0 = c[0], p2 = c[2];
-        const uint32_t hi0 = __umulhi(0xD2511F53u, p0), lo0 = 0xD2511F53u * p0;
-        const uint32_t hi1 = __umulhi(0xCD9E8D57u, p2), lo1 = 0xCD9E8D57u * p2;
-        c[0] = hi1 ^ c[1] ^ k0;
-        c[1] = lo1;
-        c[2] = hi0 ^ c[3] ^ k1;
-        c[3] = lo0;
+        const uint64_t m0 = (uint64_t)0xD2511F53u * c[0], m1 = (uint64_t)0xCD9E8D57u * c[2];
+        c[0] = (uint32_t)(m1 >> 32) ^ c[1] ^ k0;
+        c[1] = (uint32_t)m1;
+        c[2] = (uint32_t)(m0 >> 32) ^ c[3] ^ k1;
+        c[3] = (uint32_t)m0;
     }
 }
 

@@ -15,11 +15,12 @@
 // neighbours above and below are rarely 16-byte aligned, and reading those
 // float by float, under a branch each, made four 797x803 images take 49 us
 // instead of 27.  A thread's pixel follows from its block's (one 64-bit
-// division, uniform over the block) by 32-bit divisions.  The loss terms of a float are
-// its squared difference and its differences to the right and lower
+// division, uniform over the block) by 32-bit divisions.  The loss terms of a
+// float are its squared difference and its differences to the right and lower
 // neighbours; a block sums them in FP32, and a second kernel adds each
 // image's block sums in FP64 in a fixed order, so the result does not depend
-// on scheduling.  With lambda = 0 (the plain L2 loss) no neighbour is read.  Up to kLossBatch images travel in the kernel arguments.
+// on scheduling.  With lambda = 0 (the plain L2 loss) no neighbour is read.
+// Up to kLossBatch images travel in the kernel arguments.
 #include "dpr_internal.h"
 
 namespace dpr {
