@@ -186,7 +186,13 @@ __global__ __launch_bounds__(kHullThreads) void k_hull_flags_few(HullArgs a) {
 // two cameras, packs the ones still inside into LDS, and takes only these
 // through the next two, packing again.  2^24 candidates, 16 cameras: 201 us
 // (every camera for all items of a wave until none was inside: 414).
+// Where more than kHullDense items are left after the first two, packing costs
+// more than the lanes it saves: those are walked through the other cameras
+// without it, four items to a lane, so that four lookups are in flight (a third
+// of 2^24 candidates inside all 16 masks: predicate 0.44 ms, packed 0.57, the
+// form before 0.53; with a twentieth inside, 257 us a call, always packed 260).
 constexpr int kHullFirst = 2;
+constexpr uint32_t kHullDense = 64 * kHullPer * 3 / 8;
 
 __global__ __launch_bounds__(kHullThreads) void k_hull_flags_many(HullArgs a) {
     constexpr uint32_t kItems = 64 * kHullPer;                // of a wave
@@ -204,7 +210,7 @@ __global__ __launch_bounds__(kHullThreads) void k_hull_flags_many(HullArgs a) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     if (lane < kItems / 32) s_bits[wave][lane] = 0u;
-    uint32_t n = 0;                                           // items still inside
+    uint32_t n = 0, kept = 0;                                 // items still inside; and to the end
     for (int h = 0; h < kHullPer; h += kHalf) {
         float p[kHalf][3];
         bool in[kHalf];
@@ -234,6 +240,41 @@ __global__ __launch_bounds__(kHullThreads) void k_hull_flags_many(HullArgs a) {
         }
     }
     sync();
+    if (n > kHullDense) {
+        // lanes keep kHalf items each; the ones that stay set their bits here
+        uint32_t left = 0;
+        for (uint32_t b = 0; b < n; b += 64u * kHalf) {
+            float p[kHalf][3];
+            bool in[kHalf];
+#pragma unroll
+            for (int k = 0; k < kHalf; ++k) {
+                const uint32_t l = b + 64u * (uint32_t)k + lane;
+                in[k] = l < n;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) p[k][d] = in[k] ? s_p[wave][d][l] : 0.f;
+            }
+            for (int32_t i = kHullFirst; i < a.n_cams; ++i) {
+                bool any = false;
+#pragma unroll
+                for (int k = 0; k < kHalf; ++k) any = any || in[k];
+                if (__ballot(any) == 0ull) break;
+                const HullCam &c = a.cams[i];
+#pragma unroll
+                for (int k = 0; k < kHalf; ++k)
+                    if (in[k]) in[k] = inside(c, p[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < kHalf; ++k) {
+                if (in[k]) {
+                    const uint32_t j = s_j[wave][b + 64u * (uint32_t)k + lane];
+                    atomicOr(&s_bits[wave][j >> 5], 1u << (j & 31));
+                }
+                left += (uint32_t)__popcll(__ballot(in[k]));
+            }
+        }
+        kept = left;
+        n = 0;
+    }
     for (int32_t i = kHullFirst; i < a.n_cams && n > 0; i += 2) {
         uint32_t left = 0;
         for (uint32_t b = 0; b < n; b += 64) {
@@ -263,6 +304,7 @@ __global__ __launch_bounds__(kHullThreads) void k_hull_flags_many(HullArgs a) {
         sync();
         n = left;
     }
+    kept += n;
     for (uint32_t b = lane; b < n; b += 64) {
         const uint32_t j = s_j[wave][b];
         atomicOr(&s_bits[wave][j >> 5], 1u << (j & 31));
@@ -275,7 +317,7 @@ __global__ __launch_bounds__(kHullThreads) void k_hull_flags_many(HullArgs a) {
             if (base + l < a.n) a.keep[base + l] = (uint8_t)((s_bits[wave][l >> 5] >> (l & 31)) & 1u);
         }
     }
-    if (lane == 0) s_cnt[wave] = n;
+    if (lane == 0) s_cnt[wave] = kept;
     __syncthreads();
     if (tid == 0) {
         uint32_t s = 0;

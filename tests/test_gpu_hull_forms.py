@@ -38,6 +38,17 @@ def test_sample(hull, n, n_cams, capacity):
     assert np.array_equal(xyz.cpu().numpy()[:min(kept, cap)], ref)
 
 
+@pytest.mark.parametrize("radius", [0.3, 1.0, 1.35, 9.0])      # few to all stay after two cameras: packed, or not
+def test_sample_dense_hulls(hull, radius):
+    cams = workloads.disc_views(7, size=61)
+    masks = workloads.sphere_masks(cams, radius) if radius < 3 else [np.ones((c.height, c.width), np.uint8) for c in cams]
+    n = LINE + 300
+    xyz, kept = hull.hull_sample(cams, _dev(masks), 0.7 * LO, 0.7 * HI, 78, n, capacity=n)
+    rk, ref = oracle.hull_sample(cams, masks, 0.7 * LO, 0.7 * HI, 78, n, capacity=n)
+    assert kept == rk
+    assert np.array_equal(xyz.cpu().numpy()[:kept], ref)
+
+
 @pytest.mark.parametrize("n", [255, 257, LINE - 1, LINE + 1])
 @pytest.mark.parametrize("degree", [0, 3])
 def test_keep_and_filter(hull, n, degree):
