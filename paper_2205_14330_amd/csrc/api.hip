@@ -948,8 +948,14 @@ int dpr_render_forward_1(const dpr_scene *scene, const dpr_camera *cam, const dp
     const size_t pb_al = (size_t)align_up(pb);
     if (ws_needed) *ws_needed = pb_al;
     if (!ws || ws_bytes < pb_al) return fail(DPR_ERR_WORKSPACE, "workspace needs at least %zu bytes", pb_al);
+    // the plan ends with this call, so no backward state is laid out or written
+    dpr_params pr;
+    if (params) {
+        pr = *params;
+        if (pr.bwd_mode == DPR_BWD_STORED) pr.bwd_mode = DPR_BWD_RECOMPUTE;
+    }
     dpr_plan *p = nullptr;
-    int rc = dpr_plan_forward(scene, 1, &view, 1, params, ws, pb, stream, &p);
+    int rc = dpr_plan_forward(scene, 1, &view, 1, params ? &pr : nullptr, ws, pb, stream, &p);
     if (rc) return rc;
     const size_t need = pb_al + dpr_workspace_bytes(p);
     if (ws_needed) *ws_needed = need;

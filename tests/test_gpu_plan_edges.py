@@ -94,3 +94,26 @@ def test_segment_lengths_agree(dpr, n, mode):
     for a, b, name in zip(few, many, NAMES):
         # FP32 sums over the same pixels from checkpoints at other positions; as stored against recomputed state
         assert np.abs(a - b).max() <= 1e-5 * np.abs(a).max(), name
+
+
+@pytest.mark.parametrize("mode", ["stored", "recompute"])
+def test_single_view_workspace_holds_no_backward_state(dpr, mode):
+    """dpr_render_forward_1 asks for the plan and its lists only, in either mode, and renders what the plan does."""
+    import ctypes
+    import torch
+    sc = workloads.small_scene(210, 3000, extent=0.6)
+    cam = workloads.random_sphere_camera(np.random.default_rng(210), 70, 50)
+    params = dpr.RenderParams(bwd_mode=mode)
+    plan = gpu_plan([sc], [(0, cam)], dpr.RenderParams(bwd_mode="recompute"))
+    inf = plan.info()
+    lib = dpr.load()
+    st = dpr.SceneTensors.from_numpy(sc)
+    c_sc, c_cam, c_params = st.c_struct(), dpr.camera_struct(cam), params.to_c()
+    img, tr = torch.empty((50, 70, 3), device="cuda"), torch.empty((50, 70), device="cuda")
+    size = (inf.plan_ws_bytes + 255) // 256 * 256 + inf.fwd_ws_bytes
+    ws, need = torch.empty(size, dtype=torch.uint8, device="cuda"), ctypes.c_size_t()
+    rc = lib.dpr_render_forward_1(ctypes.byref(c_sc), ctypes.byref(c_cam), ctypes.byref(c_params), img.data_ptr(),
+                                  tr.data_ptr(), ws.data_ptr(), size, ctypes.byref(need), None)
+    torch.cuda.synchronize()
+    assert rc == 0 and need.value == size
+    assert torch.equal(img, plan.images[0]) and torch.equal(tr, plan.trans[0])
