@@ -193,8 +193,9 @@ int dpr_plan_forward(const dpr_scene *scenes, int32_t n_scenes,
 /* Bytes of the forward workspace, known after dpr_plan_forward: the per-tile
  * pair lists and, in stored mode, the state the backward reads (per pixel the
  * blend end and final (T, I); per tile a (T, I) checkpoint of every pixel each
- * 256 list positions; the backward's work items), up to 16 B per pair + 20 B
- * per pixel on top of the 4 B per pair of the lists. */
+ * 256 list positions, or 128 in small plans; the backward's work items), on top
+ * of the 4 B per pair of the lists: 4 KB per tile, 20 B per pixel, and up to
+ * 16 B per pair (small plans, below 2^22 pairs: up to 32). */
 size_t dpr_workspace_bytes(const dpr_plan *plan);
 
 /* Emits the per-tile depth-ordered splat lists and composites every view front
