@@ -64,8 +64,8 @@ hipError_t launch_chamfer_grid(uint32_t n1, const float *s1, uint32_t n2, const 
 // out_sh[e] (e = query k3 + attribute): the mean of the attribute over the
 // query's neighbours, FP64 in neighbour order.  A thread per value: a row's
 // values are neighbouring lanes, so each neighbour's row is one run of loads.
-__global__ void k_topk_mean(const int32_t *idx, const float *sh1, uint64_t values, uint32_t k3, int K, int keff,
-                            float *out_sh) {
+__global__ void k_topk_mean(const int32_t *idx, const float *sh1, uint32_t n1, uint64_t values, uint32_t k3, int K,
+                            int keff, float *out_sh) {
     for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < values;
          e += (uint64_t)gridDim.x * blockDim.x) {
         const uint64_t j = e / k3;
@@ -73,7 +73,7 @@ __global__ void k_topk_mean(const int32_t *idx, const float *sh1, uint64_t value
         const int32_t *nb = idx + j * (uint32_t)K;
         double acc = 0.0;
 #pragma unroll 4
-        for (int k = 0; k < keff; ++k) acc += (double)sh1[(uint64_t)k3 * (uint32_t)nb[k] + a];
+        for (int k = 0; k < keff; ++k) acc += (double)sh1[(uint64_t)k3 * min((uint32_t)nb[k], n1 - 1u) + a];
         out_sh[e] = (float)(acc / (double)keff);
     }
 }
@@ -98,8 +98,8 @@ hipError_t launch_topk_grid(uint32_t n1, const float *s1, const float *sh1, uint
     if (e != hipSuccess) return e;
     const uint64_t values = (uint64_t)n2 * (uint32_t)k3;
     const uint64_t mean_blocks = (values + 255) / 256;
-    hipLaunchKernelGGL(k_topk_mean, dim3((uint32_t)(mean_blocks < 65536 ? mean_blocks : 65536)), dim3(256), 0, st, q.idx, sh1, values,
-                       (uint32_t)k3, K, q.keff, out_sh);
+    hipLaunchKernelGGL(k_topk_mean, dim3((uint32_t)(mean_blocks < 65536 ? mean_blocks : 65536)), dim3(256), 0, st, q.idx, sh1, n1,
+                       values, (uint32_t)k3, K, q.keff, out_sh);
     return hipGetLastError();
 }
 

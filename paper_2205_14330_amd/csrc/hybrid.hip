@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kHyThreads) void k_generate(CloudOut c, uint32_t m,
         const int32_t *nb = idx + (size_t)i * K;
         double sum = 0.0;
 #pragma unroll 8
-        for (int q = 0; q < keff; ++q) sum += (double)col[(uint64_t)(uint32_t)nb[q] * stride];
+        for (int q = 0; q < keff; ++q) sum += (double)col[(uint64_t)min((uint32_t)nb[q], m - 1u) * stride];
         col[((uint64_t)m + i) * stride] = (float)(sum / (double)keff);
     }
 }

@@ -47,8 +47,10 @@ constexpr uint32_t kOccWords = kOccAxis * kOccAxis * kOccAxis / 32;
 constexpr uint32_t kNnMaxWalk = 1024;                   // candidates a single thread walks
 
 struct GridGeom {
-    float lo[3];
+    float lo[3];                // -infinity on an axis without a finite extent: one cell, which ends nowhere
     float h, inv;               // cell edge and its inverse (0: one cell)
+    float hs;                   // the edge as the bounds on distances take it; 0, which bounds nothing, if its
+                                // square would leave the range in which the distances' rounding is relative
     uint32_t nx, ny, nz;
 };
 
@@ -255,14 +257,14 @@ __device__ __forceinline__ GridGeom grid_geometry(const NnCloud &c, const float 
     GridGeom g;
     float e[3];
     for (int k = 0; k < 3; ++k) {
-        g.lo[k] = box[k];
         const float d = box[3 + k] - box[k];
+        g.lo[k] = d >= 0.f && d < INFINITY ? box[k] : -INFINITY;
         e[k] = d > 0.f && d < INFINITY ? d : 0.f;
     }
     const float m0 = fmaxf(e[0], fmaxf(e[1], e[2])), m2 = fminf(e[0], fminf(e[1], e[2]));
     const float m1 = fmaxf(fminf(e[0], e[1]), fminf(fmaxf(e[0], e[1]), e[2]));
     g.nx = g.ny = g.nz = 1u;
-    g.h = g.inv = 0.f;
+    g.h = g.inv = g.hs = 0.f;
     if (!(m0 > 0.f)) return g;
     const float G = (float)c.occ_axis;
     const float cells = fmaxf((float)c.n / c.density, 1.f);
@@ -281,6 +283,8 @@ __device__ __forceinline__ GridGeom grid_geometry(const NnCloud &c, const float 
         if ((fx + 1.f) * fy * fz <= 0.999f * (float)c.max_cells) {      // nx + 1 table entries per row
             g.h = h;
             g.inv = inv;
+            const float hs = 0.9999f * h;
+            g.hs = hs * hs >= 1e-36f && hs * hs < INFINITY ? hs : 0.f;
             g.nx = (uint32_t)fx;
             g.ny = (uint32_t)fy;
             g.nz = (uint32_t)fz;
@@ -495,18 +499,22 @@ __device__ __forceinline__ float nn_margin(const GridGeom &g) {
 // The squared distance below which no point outside the cube of r cells around
 // (cx, cy, cz) can be: the nearest face that has cells behind it, in cells from
 // the query at (tx, ty, tz), less margins for the rounding of the cell
-// coordinates and of the distances.  Infinite if the cube holds the whole grid.
+// coordinates and of the distances.  Infinite if, and only if, the cube holds
+// the whole grid: of a face at no finite distance (the query is not finite, or
+// far beyond the grid) nothing is said that a K-th distance could be below, as
+// all distances of such a query are infinite or NaN.
 __device__ __forceinline__ float nn_bound(const GridGeom &g, float tx, float ty, float tz, int cx, int cy, int cz, int r) {
+    constexpr float kMost = 3.4028235e38f;               // the largest finite value
     float f = INFINITY;
-    if (cx - r > 0) f = fminf(f, tx - (float)(cx - r));
-    if (cy - r > 0) f = fminf(f, ty - (float)(cy - r));
-    if (cz - r > 0) f = fminf(f, tz - (float)(cz - r));
-    if (cx + r + 1 < (int)g.nx) f = fminf(f, (float)(cx + r + 1) - tx);
-    if (cy + r + 1 < (int)g.ny) f = fminf(f, (float)(cy + r + 1) - ty);
-    if (cz + r + 1 < (int)g.nz) f = fminf(f, (float)(cz + r + 1) - tz);
+    if (cx - r > 0) f = fminf(fminf(f, tx - (float)(cx - r)), kMost);
+    if (cy - r > 0) f = fminf(fminf(f, ty - (float)(cy - r)), kMost);
+    if (cz - r > 0) f = fminf(fminf(f, tz - (float)(cz - r)), kMost);
+    if (cx + r + 1 < (int)g.nx) f = fminf(fminf(f, (float)(cx + r + 1) - tx), kMost);
+    if (cy + r + 1 < (int)g.ny) f = fminf(fminf(f, (float)(cy + r + 1) - ty), kMost);
+    if (cz + r + 1 < (int)g.nz) f = fminf(fminf(f, (float)(cz + r + 1) - tz), kMost);
     if (f == INFINITY) return INFINITY;
-    f = fmaxf(f - nn_margin(g), 0.f) * 0.9999f * g.h;
-    return f * f;
+    f = fmaxf(f - nn_margin(g), 0.f) * g.hs;
+    return fminf(f * f, kMost);
 }
 
 // Four candidates from i on, the last of the run repeated past its end.
@@ -516,8 +524,13 @@ __device__ __forceinline__ void nn_load4(const float4 *pts, uint32_t i, uint32_t
 }
 
 // Key of a candidate, ~0 if it is not one.
+template <bool SELF>
+__device__ __forceinline__ float nn_between(const float4 &q, const float4 &p) {
+    return SELF ? nn_dist2(p.x, p.y, p.z, q.x, q.y, q.z) : nn_dist2(q.x, q.y, q.z, p.x, p.y, p.z);
+}
+template <bool SELF>
 __device__ __forceinline__ unsigned long long nn_key(const float4 &q, const float4 &p, bool ok) {
-    const float d = nn_dist2(q.x, q.y, q.z, p.x, p.y, p.z);
+    const float d = nn_between<SELF>(q, p);
     return ok ? ((unsigned long long)__float_as_uint(d) << 32) | __float_as_uint(p.w) : ~0ull;
 }
 
@@ -531,7 +544,7 @@ __device__ __forceinline__ void nn_walk(const NnQuery &a, const float4 &q, uint2
         nn_load4(a.pts, i, run.y, p);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            nn_insert<KMAX>(best, a.keff, nn_key(q, p[u], i + u < run.y && (!SELF || __float_as_uint(p[u].w) != self)),
+            nn_insert<KMAX>(best, a.keff, nn_key<SELF>(q, p[u], i + u < run.y && (!SELF || __float_as_uint(p[u].w) != self)),
                             worst);
     }
 }
@@ -578,7 +591,7 @@ __device__ __forceinline__ void nn_walk_runs(const NnQuery &a, const float4 &q, 
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const unsigned long long x = nn_key(q, c[u], (uint32_t)u < n && (!SELF || __float_as_uint(c[u].w) != self));
+            const unsigned long long x = nn_key<SELF>(q, c[u], (uint32_t)u < n && (!SELF || __float_as_uint(c[u].w) != self));
             if (x < worst) s_buf[held++][tid] = x;
         }
         if (__ballot(held > kNnBuf - 4) != 0ull || __ballot(more) == 0ull) {
@@ -669,7 +682,7 @@ static __global__ __launch_bounds__(kGridThreads) void k_nn_query(NnQuery a) {
         }
     }
     // distances to the neighbouring rows of cells, with the margins of nn_bound
-    const float m = nn_margin(g), hs = 0.9999f * g.h;
+    const float m = nn_margin(g), hs = g.hs;
     const float yl = fmaxf(ty - (float)cy - m, 0.f) * hs, yh = fmaxf((float)(cy + 1) - ty - m, 0.f) * hs;
     const float zl = fmaxf(tz - (float)cz - m, 0.f) * hs, zh = fmaxf((float)(cz + 1) - tz - m, 0.f) * hs;
     const auto far = [&](int k) {
@@ -727,7 +740,7 @@ static __global__ __launch_bounds__(kGridThreads) void k_nn_nearest(NnQuery qa, 
     const uint32_t self = __float_as_uint(q.w);
     const float tx = (q.x - g.lo[0]) * g.inv, ty = (q.y - g.lo[1]) * g.inv, tz = (q.z - g.lo[2]) * g.inv;
     const int cx = (int)grid_axis(tx, g.nx), cy = (int)grid_axis(ty, g.ny), cz = (int)grid_axis(tz, g.nz);
-    const float m = nn_margin(g), hs = 0.9999f * g.h;
+    const float m = nn_margin(g), hs = g.hs;
     const float bound = nn_bound(g, tx, ty, tz, cx, cy, cz, 1), bound2 = nn_bound(g, tx, ty, tz, cx, cy, cz, 2);
     unsigned long long best = ~0ull;
     bool on = valid && a.keff > 0, left = false;          // the same in a query's lanes
@@ -763,7 +776,7 @@ static __global__ __launch_bounds__(kGridThreads) void k_nn_nearest(NnQuery qa, 
                 for (uint32_t d = kNearLanes / 2; d >= 1; d >>= 1)
                     if (s_pre[lo + d] <= c) lo += d;
                 const float4 p = a.pts[s_beg[lo] + (c - s_pre[lo])];
-                const unsigned long long x = nn_key(q, p, !SELF || __float_as_uint(p.w) != self);
+                const unsigned long long x = nn_key<SELF>(q, p, !SELF || __float_as_uint(p.w) != self);
                 best = x < best ? x : best;
             }
         }
@@ -815,7 +828,7 @@ __device__ __forceinline__ void nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
     unsigned long long best = ~0ull, worst = ~0ull;      // worst: lane keff - 1's
     int half = 0;
     s.list[0][wave][lane] = s.list[1][wave][lane] = ~0ull;
-    const float m = nn_margin(g), hs = 0.9999f * g.h;
+    const float m = nn_margin(g), hs = g.hs;
     int done = -1;                                       // the cube of `done` cells has been walked
     bool any = false;                                    // a candidate was met (the same in every lane)
     for (int r = 1;;) {
@@ -847,7 +860,7 @@ __device__ __forceinline__ void nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
                     const float room = __uint_as_float((uint32_t)(worst >> 32)) / (hs * hs) - (fy * fy + fz * fz);
                     if (room < 0.f) {
                         v = u - 1;
-                    } else if (room < 1e9f) {
+                    } else if (room < 1e9f && fabsf(tx) < INFINITY) {
                         const float x = sqrtf(room) + m;
                         u = max(u, (int)fmaxf(fminf(tx - x, 1e9f), 0.f));
                         v = min(v, (int)fmaxf(fminf(tx + x, 1e9f), -1.f));
@@ -884,7 +897,7 @@ __device__ __forceinline__ void nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
                             if (s.pre[wave][lo + d] <= c) lo += d;
                         const float4 p = a.pts[s.beg[wave][lo] + (c - s.pre[wave][lo])];
                         const uint32_t j = __float_as_uint(p.w);
-                        const float d = nn_dist2(q.x, q.y, q.z, p.x, p.y, p.z);
+                        const float d = nn_between<SELF>(q, p);
                         if ((!SELF || j != self) && (!FILTERED || a.alive[j])) x = ((unsigned long long)__float_as_uint(d) << 32) | j;
                     }
                     if (__ballot(x < worst) == 0ull) continue;
@@ -928,7 +941,7 @@ __device__ __forceinline__ void nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
         nn_wave_sync();
     }
     if ((int)lane < a.K) {
-        const bool ok = (int)lane < a.keff;
+        const bool ok = (int)lane < a.keff && best != ~0ull;
         const uint32_t j = (uint32_t)(best & 0xFFFFFFFFull), i = FILTERED ? a.pos[self] : self;
         a.idx[(size_t)i * a.K + lane] = !ok ? -1 : (int32_t)(FILTERED ? a.pos[j] : j);
         if (MODE == kNnIndexDist) a.d2[(size_t)i * a.K + lane] = ok ? __uint_as_float((uint32_t)(best >> 32)) : 0.f;
