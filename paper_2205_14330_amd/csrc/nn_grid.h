@@ -420,7 +420,7 @@ struct NnQuery {
     const float4 *pts;
     uint32_t *list, *list_n;    // [nq] queries left for a wave each, their number (cleared before)
     // outputs, by the query's index
-    unsigned long long *key;    // kNnKey: the nearest's (d2 bits << 32 | index)
+    unsigned long long *key;    // kNnKey: the nearest's (d2 bits << 32 | index), ~0 if none is at a finite distance
     int32_t *idx;               // kNnIndex, kNnIndexDist, kNnSpread: [nq][K], -1 past keff
     float *d2;                  // kNnIndexDist: [nq][K], 0 past keff
     uint32_t *keep;             // kNnSpread: 1 if the spread of the distances is at most eps
@@ -473,11 +473,16 @@ __device__ __forceinline__ uint32_t nn_spread_keep(const NnQuery &a, const unsig
     return a.keff > 0 && delta > a.eps ? 0u : 1u;
 }
 
+// The nearest's key, ~0 (none) if it is at no finite distance, as in nn_brute.
+__device__ __forceinline__ unsigned long long nn_finite(unsigned long long key) {
+    return key < 0x7F800000ull << 32 ? key : ~0ull;
+}
+
 // The results of one query (one lane).
 template <int KMAX, int MODE>
 __device__ __forceinline__ void nn_write(const NnQuery &a, uint32_t i, const unsigned long long (&best)[KMAX]) {
     if (MODE == kNnKey) {
-        a.key[i] = best[0];
+        a.key[i] = nn_finite(best[0]);
         return;
     }
     if (MODE == kNnSpread) a.keep[i] = nn_spread_keep<KMAX>(a, best);
@@ -931,7 +936,7 @@ __device__ __forceinline__ void nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
         r += any ? (r + 1) / 2 : r;
     }
     if (MODE == kNnKey) {
-        if (lane == 0) a.key[self] = best;
+        if (lane == 0) a.key[self] = nn_finite(best);
         return;
     }
     if (MODE == kNnSpread) {

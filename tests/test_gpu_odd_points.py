@@ -46,6 +46,27 @@ def test_topk_by_grid_and_by_brute_force(dpr, name, K, odd):
     assert torch.equal(idx, ridx) and torch.equal(out, ref)
 
 
+@pytest.mark.parametrize("odd", ["s1", "s2", "both"])
+@pytest.mark.parametrize("name", ["nan", "nan coordinate", "inf", "far", "huge", "tiny", "nan axis", "inf axis",
+                                  "all nan"])
+def test_chamfer_by_grid_and_by_brute_force(dpr, name, odd):
+    """Indices and Eq. (9) as by brute force (with its smaller workspace); the gradient to the order of its FP64 sums."""
+    import torch
+    from paper_2205_14330_amd import _abi, chamfer as cf
+    s1 = _t(clouds("ball", 25)[0][:9000] if odd == "s2" else odd_cloud(name, 9000))
+    s2 = _t(clouds("ball", 25)[1][:8900] if odd == "s1" else odd_cloud(name, 8900, 1))
+    out = cf.chamfer(s1, s2, grad=True, nn=True)
+    L = _abi.load()
+    ws = torch.empty(L.dpr_chamfer_ws_bytes(len(s1), len(s2)) // 2, dtype=torch.uint8, device="cuda")
+    ref = {k: torch.empty_like(v) for k, v in out.items()}
+    _abi.check(L.dpr_chamfer(len(s1), s1.data_ptr(), len(s2), s2.data_ptr(), ref["cd"].data_ptr(), ref["grad2"].data_ptr(),
+                             ref["nn12"].data_ptr(), ref["nn21"].data_ptr(), ws.data_ptr(), ws.numel(),
+                             torch.cuda.current_stream().cuda_stream))
+    assert torch.equal(out["nn12"], ref["nn12"]) and torch.equal(out["nn21"], ref["nn21"])
+    assert torch.equal(out["cd"].nan_to_num(-1.0), ref["cd"].nan_to_num(-1.0))
+    torch.testing.assert_close(out["grad2"], ref["grad2"], rtol=1e-6, atol=0.0, equal_nan=True)
+
+
 @pytest.mark.parametrize("K", [4, 9])
 @pytest.mark.parametrize("name", ["nan", "nan coordinate", "inf", "far", "huge", "tiny"])
 def test_knn_by_thread_and_by_wave(dpr, name, K):

@@ -17,6 +17,11 @@ def grid(tmp_path_factory):
 
 
 @pytest.fixture(scope="module")
+def brute(tmp_path_factory):
+    return compile_harness("chamfer_host", tmp_path_factory.mktemp("hostbuild"))
+
+
+@pytest.fixture(scope="module")
 def hybrid(tmp_path_factory):
     return compile_harness("hybrid_host", tmp_path_factory.mktemp("hostbuild"))
 
@@ -44,6 +49,39 @@ def test_topk(grid, tmp_path, name, K, odd):
     idx, _ = nearest(b, a, K)
     assert np.array_equal(_read(tmp_path, "idx.bin", np.int32, (-1, K)), idx)
     assert np.array_equal(_read(tmp_path, "out_sh.bin", np.float32, (-1, 4, 3)), mean_rows(sh, idx))
+
+
+@pytest.mark.parametrize("odd", ["s1", "s2", "both"])
+@pytest.mark.parametrize("name", NAMES)
+def test_chamfer(grid, brute, tmp_path, name, odd):
+    """Through the grid and by brute force: a point at no finite distance of any other has no nearest (-1); it takes
+    part in no other point's gradient."""
+    s1 = clouds("ball")[0][:160] if odd == "s2" else odd_cloud(name, 160)
+    s2 = clouds("ball")[1][:150] if odd == "s1" else odd_cloud(name, 150, 1)
+    n12, n21, cd, g = _eq9(s1, s2)
+    for exe in (grid, brute):
+        run(exe, tmp_path, "chamfer", {"s1": s1, "s2": s2})
+        assert np.array_equal(_read(tmp_path, "nn12.bin", np.int32, (-1,)), n12)
+        assert np.array_equal(_read(tmp_path, "nn21.bin", np.int32, (-1,)), n21)
+        np.testing.assert_allclose(_read(tmp_path, "cd.bin", np.float64, (1,))[0], cd, rtol=1e-12)
+        # rounding of FP64 sums in another order, then float32
+        np.testing.assert_allclose(_read(tmp_path, "grad2.bin", np.float32, (-1, 3)), g, rtol=1e-6,
+                                   atol=1e-7 * np.nanmax(np.abs(np.where(np.isfinite(g), g, 0.0))))
+
+
+def _eq9(s1, s2):
+    """nn12, nn21, Eq. (9) and its gradient, FP64."""
+    def nn(q, c):
+        i, d = nearest(q, c, 1)
+        return np.where(d[:, 0] < np.inf, i[:, 0], -1), np.where(d[:, 0] < np.inf, d[:, 0], np.nan).astype(np.float64)
+    (n12, d12), (n21, d21) = nn(s1, s2), nn(s2, s1)
+    a, b = s1.astype(np.float64), s2.astype(np.float64)
+    with np.errstate(all="ignore"):
+        g = 2.0 / len(b) * (b - np.where(n21[:, None] >= 0, a[n21], np.nan))
+        for i in np.nonzero(n12 >= 0)[0]:
+            g[n12[i]] += 2.0 / len(a) * (b[n12[i]] - a[i])
+        cd = d12.sum() / len(a) + d21.sum() / len(b)
+    return n12, n21, cd, g
 
 
 def _update(red, K, eps):
