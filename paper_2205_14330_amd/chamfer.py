@@ -10,7 +10,7 @@ import torch
 
 from . import _abi
 from ._abi import check, load
-from .renderer import _stream_handle
+from .renderer import _scratch, _stream_handle
 
 
 def _xyz(t: torch.Tensor, name: str):
@@ -56,7 +56,7 @@ def topk_sh(s1: torch.Tensor, sh1: torch.Tensor, s2: torch.Tensor, K: int, with_
     out = torch.empty((n2,) + tuple(sh1.shape[1:]), dtype=torch.float32, device=s1.device)
     idx = torch.empty((n2, K), dtype=torch.int32, device=s1.device) if with_index else None
     # 0 (bad sizes): the call itself says which
-    ws = torch.empty(max(int(lib.dpr_topk_sh_ws_bytes(n1, n2, int(K))), 1), dtype=torch.uint8, device=s1.device)
+    ws = _scratch(max(int(lib.dpr_topk_sh_ws_bytes(n1, n2, int(K))), 1), s1.device, stream)
     check(lib.dpr_topk_sh_ws(n1, s1.data_ptr(), sh1.data_ptr(), n2, s2.data_ptr(), deg, int(K), out.data_ptr(),
                              idx.data_ptr() if idx is not None else None, ws.data_ptr(), int(ws.numel()),
                              _stream_handle(stream)))

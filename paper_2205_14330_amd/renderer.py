@@ -99,6 +99,16 @@ def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
     return int(s.cuda_stream)
 
 
+def _scratch(nbytes: int, device, stream: Optional[torch.cuda.Stream]) -> torch.Tensor:
+    """Scratch memory of one call on `stream` (None: the current stream), from that stream's pool.  The call drops it
+    on return, while its kernels still run: memory of another stream's pool could then be given to a tensor of that
+    stream, which nothing orders behind those kernels."""
+    if stream is None:
+        return torch.empty(int(nbytes), dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(int(nbytes), dtype=torch.uint8, device=device)
+
+
 class Workspace:
     """Device buffers for the plan, forward and backward workspaces, reused by
     successive plans and grown geometrically (never shrunk), so a loop whose
