@@ -36,7 +36,7 @@ def chamfer(s1: torch.Tensor, s2: torch.Tensor, grad: bool = True, nn: bool = Fa
     nbytes = lib.dpr_chamfer_ws_bytes(n1, n2)
     if nbytes == 0:
         check(_abi.DPR_ERR_INVALID_ARG)
-    ws = torch.empty(int(nbytes), dtype=torch.uint8, device=dev)
+    ws = _scratch(nbytes, dev, stream)
     p = lambda k: out[k].data_ptr() if k in out else None
     check(lib.dpr_chamfer(n1, s1.data_ptr(), n2, s2.data_ptr(), p("cd"), p("grad2"), p("nn12"), p("nn21"),
                           ws.data_ptr(), int(nbytes), _stream_handle(stream)))

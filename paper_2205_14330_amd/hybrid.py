@@ -10,17 +10,17 @@ import torch
 
 from . import _abi
 from ._abi import check, load
-from .renderer import SceneTensors, _stream_handle
+from .renderer import SceneTensors, _scratch, _stream_handle
 
 
 def _check_scene(s: SceneTensors):
     s.c_struct()                      # validates dtype / contiguity / device
 
 
-def _ws(nbytes: int, dev) -> torch.Tensor:
+def _ws(nbytes: int, dev, stream) -> torch.Tensor:
     if nbytes == 0:
         check(_abi.DPR_ERR_INVALID_ARG)
-    return torch.empty(int(nbytes), dtype=torch.uint8, device=dev)
+    return _scratch(nbytes, dev, stream)
 
 
 def knn(xyz: torch.Tensor, K: int, stream: Optional[torch.cuda.Stream] = None) -> Tuple[torch.Tensor, torch.Tensor]:
@@ -33,7 +33,7 @@ def knn(xyz: torch.Tensor, K: int, stream: Optional[torch.cuda.Stream] = None) -
     m = int(xyz.shape[0])
     idx = torch.empty((m, K), dtype=torch.int32, device=xyz.device)
     d2 = torch.empty((m, K), dtype=torch.float32, device=xyz.device)
-    ws = _ws(lib.dpr_knn_ws_bytes(m, K), xyz.device)
+    ws = _ws(lib.dpr_knn_ws_bytes(m, K), xyz.device, stream)
     check(lib.dpr_knn(m, xyz.data_ptr(), K, idx.data_ptr(), d2.data_ptr(), ws.data_ptr(), int(ws.numel()),
                       _stream_handle(stream)))
     return idx, d2
@@ -58,7 +58,7 @@ def voxel_reduce(scene: SceneTensors, N: int, stream: Optional[torch.cuda.Stream
     lib = load()
     n = scene.n
     out = _empty_like_scene(scene, n)
-    ws = _ws(lib.dpr_hybrid_ws_bytes(n, scene.sh_degree, 1), scene.xyz.device)
+    ws = _ws(lib.dpr_hybrid_ws_bytes(n, scene.sh_degree, 1), scene.xyz.device, stream)
     cnt = ctypes.c_int64(0)
     check(lib.dpr_voxel_reduce(n, scene.sh_degree, scene.xyz.data_ptr(), scene.sh.data_ptr(),
                                scene.opacity.data_ptr(), scene.radius.data_ptr(), int(N), out.xyz.data_ptr(),
@@ -75,7 +75,7 @@ def hybrid_update(scene: SceneTensors, N: int, K: int, eps: float,
     lib = load()
     n = scene.n
     out = _empty_like_scene(scene, 2 * n)
-    ws = _ws(lib.dpr_hybrid_ws_bytes(n, scene.sh_degree, K), scene.xyz.device)
+    ws = _ws(lib.dpr_hybrid_ws_bytes(n, scene.sh_degree, K), scene.xyz.device, stream)
     counts = (ctypes.c_int64 * 3)()
     check(lib.dpr_hybrid_update(n, scene.sh_degree, scene.xyz.data_ptr(), scene.sh.data_ptr(),
                                 scene.opacity.data_ptr(), scene.radius.data_ptr(), int(N), int(K), float(eps),

@@ -381,7 +381,7 @@ def loss_l2_tv(renders: Sequence[torch.Tensor], targets: Sequence[torch.Tensor],
     nb = int(lib.dpr_loss_ws_bytes(n, W, H))
     if nb == 0:
         check(_abi.DPR_ERR_INVALID_ARG)
-    ws = workspace.get("loss", nb) if workspace is not None else torch.empty(nb, dtype=torch.uint8, device=dev)
+    ws = workspace.get("loss", nb) if workspace is not None else _scratch(nb, dev, stream)
     loss = torch.empty(n, dtype=torch.float64, device=dev)
     P = _abi.ptr_array
     check(lib.dpr_loss_l2_tv(n, P([r.data_ptr() for r in renders]), P([t.data_ptr() for t in targets]), W, H,

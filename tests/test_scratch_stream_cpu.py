@@ -7,7 +7,9 @@ import contextlib
 import pytest
 import torch
 
-from paper_2205_14330_amd import chamfer
+import workloads
+from paper_2205_14330_amd import chamfer, hull, hybrid, renderer
+from paper_2205_14330_amd.renderer import SceneTensors
 
 
 class _Cuda(torch.Tensor):
@@ -34,7 +36,25 @@ def _topk(stream):
     chamfer.topk_sh(_dev(9, 3), _dev(9, 4, 3), _dev(5, 3), 4, stream=stream)
 
 
-CALLS = {"topk_sh": _topk}
+def _scene():
+    return SceneTensors(_dev(9, 3), _dev(9, 4, 3), _dev(9), _dev(9))
+
+
+def _views():
+    return [workloads.orbit_camera(0, 8, 8, 6)], [torch.zeros(6, 8, dtype=torch.uint8).as_subclass(_Cuda)]
+
+
+CALLS = {
+    "topk_sh": _topk,
+    "chamfer": lambda s: chamfer.chamfer(_dev(9, 3), _dev(5, 3), stream=s),
+    "knn": lambda s: hybrid.knn(_dev(9, 3), 4, stream=s),
+    "voxel_reduce": lambda s: hybrid.voxel_reduce(_scene(), 4, stream=s),
+    "hybrid_update": lambda s: hybrid.hybrid_update(_scene(), 4, 4, 0.1, stream=s),
+    "hull_sample": lambda s: hull.hull_sample(*_views(), (0, 0, 0), (1, 1, 1), 1, 9, stream=s),
+    "consistency": lambda s: hull.consistency(_dev(9, 3), *_views(), stream=s),
+    "consistency_filter": lambda s: hull.consistency_filter(_scene(), *_views(), stream=s),
+    "loss_l2_tv": lambda s: renderer.loss_l2_tv([_dev(6, 8, 3)], [_dev(6, 8, 3)], stream=s),
+}
 
 
 @pytest.mark.parametrize("name", sorted(CALLS))
@@ -53,7 +73,8 @@ def test_scratch_is_allocated_on_the_calls_stream(monkeypatch, name):
             scratch.append(current[-1])
         return empty(*a, **k)
 
-    monkeypatch.setattr(chamfer, "load", _Lib)
+    for module in (chamfer, hybrid, hull, renderer):
+        monkeypatch.setattr(module, "load", _Lib)
     monkeypatch.setattr(torch.cuda, "stream", stream)
     monkeypatch.setattr(torch, "empty", recorded)
     side = _Stream()
