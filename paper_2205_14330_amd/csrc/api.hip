@@ -1185,11 +1185,6 @@ int dpr_consistency_filter(int64_t n, int32_t sh_degree, const float *xyz, const
 }
 
 namespace {
-// The searches of the warm start: through a grid of cells, or by brute force
-// where the clouds are so small that the grid's launches cost more.
-bool chamfer_by_grid(int64_t n1, int64_t n2) { return (double)n1 * (double)n2 >= kChamferGridPairs; }
-bool topk_by_grid(int64_t n1, int64_t n2) { return (double)n1 * (double)n2 >= kTopkGridPairs; }
-
 int check_topk(int64_t n1, const float *s1, const float *sh1, int64_t n2, const float *s2, int32_t sh_degree, int32_t K,
                const float *out_sh2) {
     if (n1 < 1 || n2 < 0 || n1 > (int64_t)0x7FFFFFFF || n2 > (int64_t)0x7FFFFFFF)
@@ -1204,7 +1199,7 @@ int check_topk(int64_t n1, const float *s1, const float *sh1, int64_t n2, const 
 
 size_t dpr_chamfer_ws_bytes(int64_t n1, int64_t n2) {
     if (n1 < 1 || n2 < 1 || n1 > (int64_t)0x7FFFFFFF || n2 > (int64_t)0x7FFFFFFF) return 0;
-    return (size_t)(chamfer_by_grid(n1, n2) ? chamfer_grid_bytes((uint64_t)n1, (uint64_t)n2)
+    return (size_t)(chamfer_by_grid((uint64_t)n1, (uint64_t)n2) ? chamfer_grid_bytes((uint64_t)n1, (uint64_t)n2)
                                        : chamfer_layout((uint64_t)n1, (uint64_t)n2).bytes);
 }
 
@@ -1218,7 +1213,7 @@ int dpr_chamfer(int64_t n1, const float *s1, int64_t n2, const float *s2, double
     if (!ws || ws_bytes < L.bytes) return fail(DPR_ERR_WORKSPACE, "workspace needs %llu bytes", (unsigned long long)L.bytes);
     if (fault_injected("launch")) return fail(DPR_ERR_HIP, "injected launch failure (DPR_FAULT=launch)");
     // a workspace of the brute-force search's size is enough for that search
-    const bool grid = chamfer_by_grid(n1, n2) && ws_bytes >= chamfer_grid_bytes((uint64_t)n1, (uint64_t)n2) &&
+    const bool grid = chamfer_by_grid((uint64_t)n1, (uint64_t)n2) && ws_bytes >= chamfer_grid_bytes((uint64_t)n1, (uint64_t)n2) &&
                       ((uintptr_t)ws & 15) == 0;
     if (grid)
         HIP_TRY(launch_chamfer_grid((uint32_t)n1, s1, (uint32_t)n2, s2, cd, grad2, nn12, nn21,
@@ -1240,7 +1235,7 @@ int dpr_topk_sh(int64_t n1, const float *s1, const float *sh1, int64_t n2, const
 
 size_t dpr_topk_sh_ws_bytes(int64_t n1, int64_t n2, int32_t K) {
     if (n1 < 1 || n2 < 0 || n1 > (int64_t)0x7FFFFFFF || n2 > (int64_t)0x7FFFFFFF || K < 1 || K > kTopkMax) return 0;
-    return (size_t)(topk_by_grid(n1, n2) ? topk_grid_bytes((uint64_t)n1, (uint64_t)n2, K) : kAlign);
+    return (size_t)(topk_by_grid((uint64_t)n1, K) ? topk_grid_bytes((uint64_t)n1, (uint64_t)n2, K) : kAlign);
 }
 
 int dpr_topk_sh_ws(int64_t n1, const float *s1, const float *sh1, int64_t n2, const float *s2, int32_t sh_degree,
@@ -1253,7 +1248,7 @@ int dpr_topk_sh_ws(int64_t n1, const float *s1, const float *sh1, int64_t n2, co
     if (((uintptr_t)ws & 15) != 0) return fail(DPR_ERR_INVALID_ARG, "the workspace must be 16-byte aligned");
     const int k3 = 3 * (sh_degree + 1) * (sh_degree + 1);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (topk_by_grid(n1, n2))
+    if (topk_by_grid((uint64_t)n1, K))
         HIP_TRY(launch_topk_grid((uint32_t)n1, s1, sh1, (uint32_t)n2, s2, k3, K, out_sh2, idx,
                                  static_cast<uint8_t *>(ws), st));
     else HIP_TRY(launch_topk_sh((uint32_t)n1, s1, sh1, (uint32_t)n2, s2, k3, K, out_sh2, idx, st));

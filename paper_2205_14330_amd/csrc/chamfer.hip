@@ -174,78 +174,16 @@ hipError_t launch_chamfer(uint32_t n1, const float *s1, uint32_t n2, const float
     return launch_chamfer_finish(n1, s1, n2, s2, cd, grad2, nn12, nn21, ws, st);
 }
 
-// Top-k: a group of kTopkLanes consecutive lanes per query y of S2.  Lane s of
-// the group scans the candidates t = s mod kTopkLanes of every LDS tile of S1
-// and keeps the KM smallest keys (d2 bits << 32 | index, ascending) it met;
-// the group's lists are then merged by exchanging them between partner lanes
-// (xor 1, 2, 4).  The keys are distinct and totally ordered, so the K smallest
-// are found exactly, whatever the split.
-constexpr int kTopkLanes = 8;
-constexpr int kTopkBlock = 256;                          // 32 queries per block
-
-template <int KM>
-__device__ __forceinline__ void topk_insert(unsigned long long (&best)[KM], int K, unsigned long long x,
-                                            unsigned long long &worst) {
-    if (x >= worst) return;
-    // keep the smaller key in each place, carry the larger one on
-#pragma unroll
-    for (int k = 0; k < KM; ++k) {
-        if (k < K) {
-            const unsigned long long lo = best[k] < x ? best[k] : x;
-            x = best[k] < x ? x : best[k];
-            best[k] = lo;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < KM; ++k)
-        if (k == K - 1) worst = best[k];
-}
-
-__device__ __forceinline__ unsigned long long shfl_xor_u64(unsigned long long v, int m) {
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, m, 64);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), m, 64);
-    return ((unsigned long long)hi << 32) | lo;
-}
-
+// Top-k: the lists of topk_brute (nn_brute.h), and one lane of a query's group
+// averages its neighbours' rows.
 template <int KM>
 __global__ __launch_bounds__(kTopkBlock) void k_topk_sh(const float *s1, const float *sh1, uint32_t n1,
                                                         const float *s2, uint32_t n2, int k3, int K,
                                                         float *out_sh, int32_t *idx) {
-    __shared__ float s_x[kNnTile], s_y[kNnTile], s_z[kNnTile];
-    const uint32_t sub = threadIdx.x % (uint32_t)kTopkLanes;
-    const uint32_t j = blockIdx.x * (uint32_t)(kTopkBlock / kTopkLanes) + threadIdx.x / (uint32_t)kTopkLanes;
-    const uint32_t jj = j < n2 ? j : 0;
-    const float qx = s2[3 * (size_t)jj], qy = s2[3 * (size_t)jj + 1], qz = s2[3 * (size_t)jj + 2];
     unsigned long long best[KM];
-#pragma unroll
-    for (int k = 0; k < KM; ++k) best[k] = ~0ull;
-    unsigned long long worst = ~0ull;
-    for (uint32_t t0 = 0; t0 < n1; t0 += kNnTile) {
-        const uint32_t tn = min((uint32_t)kNnTile, n1 - t0);
-        __syncthreads();
-        for (uint32_t t = threadIdx.x; t < tn; t += kTopkBlock) {
-            s_x[t] = s1[3 * (size_t)(t0 + t)];
-            s_y[t] = s1[3 * (size_t)(t0 + t) + 1];
-            s_z[t] = s1[3 * (size_t)(t0 + t) + 2];
-        }
-        __syncthreads();
-        for (uint32_t t = sub; t < tn; t += kTopkLanes) {
-            const float d = d2f(qx, qy, qz, s_x[t], s_y[t], s_z[t]);
-            topk_insert(best, K, ((unsigned long long)__float_as_uint(d) << 32) | (t0 + t), worst);
-        }
-    }
-    // merge the group's lists: after the exchange with lane ^ m every lane of a
-    // pair holds the K smallest of both (all lanes take part in the shuffles)
-#pragma unroll
-    for (int m = 1; m < kTopkLanes; m <<= 1) {
-        unsigned long long other[KM];
-#pragma unroll
-        for (int k = 0; k < KM; ++k) other[k] = shfl_xor_u64(best[k], m);
-#pragma unroll
-        for (int k = 0; k < KM; ++k)
-            if (k < K) topk_insert(best, K, other[k], worst);
-    }
-    if (j >= n2 || sub != 0) return;
+    topk_brute(s1, n1, s2, n2, K, blockIdx.x, best);
+    const uint32_t j = topk_query(blockIdx.x);
+    if (j >= n2 || threadIdx.x % (uint32_t)kTopkLanes != 0) return;
     const int kk = (int)min((uint32_t)K, n1);
     if (idx) {
 #pragma unroll
@@ -265,7 +203,7 @@ hipError_t launch_topk_sh(uint32_t n1, const float *s1, const float *sh1, uint32
                           float *out_sh, int32_t *idx, hipStream_t st) {
     if (n2 == 0) return hipSuccess;
     if (K < 1 || K > kTopkMax) return hipErrorInvalidValue;
-    const dim3 grid((n2 + kTopkBlock / kTopkLanes - 1) / (kTopkBlock / kTopkLanes));
+    const dim3 grid((n2 + kTopkQueries - 1) / kTopkQueries);
     if (K <= 4) {
         hipLaunchKernelGGL(k_topk_sh<4>, grid, dim3(kTopkBlock), 0, st, s1, sh1, n1, s2, n2, k3, K, out_sh, idx);
     } else if (K <= 8) {

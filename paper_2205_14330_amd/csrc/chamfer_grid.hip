@@ -1,18 +1,30 @@
 // The nearest-neighbour searches of the video warm start over a grid of cells
 // (nn_grid.h): Eq. (9) in both directions, and the k nearest points of the SH
-// transfer.  The results are those of the brute-force search bit for bit: the
-// same float32 distances, ties to the lower index.
+// transfer.  The results are those of the brute-force search: the same float32
+// distances, ties to the lower index, bit for bit (the gradient sums in FP64 in
+// the order in which the blocks finish, in either search).
 //
 // Two frames' clouds are searched through about 45 candidates per point
 // instead of the whole other cloud: Eq. (9) with its gradient of two 45k-point
 // frames takes 65 us instead of 874, ten Adam steps and the transfer of the 4
-// nearest points' SH 763 us instead of 9889.  Of the 65 us 18 are the search;
-// the rest is nine launches whose work is mostly shorter than a launch (4 to 5
-// us each).  Where the clouds do not allow that (they
-// lie apart, or crowd into a few cells), more than a quarter of the queries of
-// a direction is left over by the one-thread search, and that direction is
-// searched by brute force instead of one wave per query: the kernel for the
-// left-over queries decides it per direction from their number.
+// nearest points' SH 773 us instead of 9889.  Of the 65 us 17 are the search;
+// the rest is eight launches whose work is mostly shorter than a launch (4 to 5
+// us each).
+//
+// Where the clouds do not allow that (a far point stretches the box, they crowd
+// into a few cells, or lie apart), the first pass leaves queries over: those
+// that would walk more than an eighth of the points, or more than one thread's
+// or 16 lanes' share.  A second kernel searches on for the ones left over, a
+// wave each; if they are more than a quarter, it searches by brute force for
+// all instead (a wave that ranks a whole cloud costs about three times the
+// brute-force kernel's share of a query).  Such clouds then cost the grid on
+// top of the brute-force search.  45k points, brute force alone against this:
+// one point 1000 times as far as the others, Eq. (9) 876 and 891 us, 4 nearest
+// 1128 and 1274; three tight clusters, each cloud's elsewhere, 1427 and 1403,
+// 866 and 1205 (an eighth is walked before it is left); clouds apart, 2578 and
+// 2545, 766 and 853; every point the same, 2585 and 2535, 666 and 779.  With a
+// wave for every query, however many candidates, the 4 nearest took 3501, 2145,
+// 761 and 3072 us.
 #include "nn_brute.h"
 #include "nn_grid.h"
 
@@ -20,14 +32,35 @@
 
 namespace dpr {
 
-__global__ __launch_bounds__(kGridThreads) void k_chamfer_rest(NnQuery qa, NnQuery qb, NnJob ja, NnJob jb) {
+// Brute force below: the grid's launches take some 30 us however small the
+// clouds are.  Eq. (9), brute force against grid: 8000 x 8000 points 41 and 45
+// us, 12000 x 12000 78 and 47; few points are searched fast however many search
+// them: 300 x 300k 116 and 189, 2000 x 45k 63 and 57.
+bool chamfer_by_grid(uint64_t n1, uint64_t n2) {
+    return (n1 < n2 ? n1 : n2) >= 2000 && (double)n1 * (double)n2 >= 6.4e7;
+}
+// The k nearest by brute force take a time by n1 and K (lanes walk n1 / 8
+// points each), up to some 45k queries.  10k queries, brute force against grid,
+// and on crowded points: K = 4, n1 = 1000 52 and 48 us (47 and 91), 1500 66 and
+// 48, 3000 105 and 48; K = 8, n1 = 300 52 and 51 (51 and 72), 600 69 and 51;
+// K = 16, n1 = 150 83 and 53, 300 104 and 54 (99 and 72).
+bool topk_by_grid(uint64_t n1, int K) { return n1 >= (K <= 4 ? 1500u : K <= 8 ? 600u : 300u); }
+
+// The most neighbours for which many left over are searched by brute force: a
+// wave's list costs the same for any K, the brute force's insertions grow with
+// it (45k points in three clusters: K = 12 2.7 ms by brute force, 2.8 by wave;
+// with a far point 4.6 and 3.8).
+constexpr int kTopkBruteK = 8;
+
+// Registers for six waves per SIMD: the blocks of 45k queries by brute force then run all at once.
+__global__ __launch_bounds__(kGridThreads, 6) void k_chamfer_rest(NnQuery qa, NnQuery qb, NnJob ja, NnJob jb) {
     __shared__ NnRestLds s;
     const bool first = blockIdx.x < ja.qblocks;
     const NnQuery &q = first ? qa : qb;
     const NnJob &j = first ? ja : jb;
     const uint32_t qblk = first ? blockIdx.x : blockIdx.x - ja.qblocks;
     const uint32_t n = *q.list_n;
-    if (n > q.nq / 4u) {
+    if (n > q.list_most) {
         nn_brute(j, qblk, blockIdx.y);
         return;
     }
@@ -53,6 +86,8 @@ hipError_t launch_chamfer_grid(uint32_t n1, const float *s1, uint32_t n2, const 
     NnQuery q12 = grid_query(a, b, 1, n2), q21 = grid_query(b, a, 1, n1);
     q12.key = reinterpret_cast<unsigned long long *>(ws + L.key12);
     q21.key = reinterpret_cast<unsigned long long *>(ws + L.key21);
+    q12.list_most = n1 / 4u;
+    q21.list_most = n2 / 4u;
     const uint32_t b1 = (n1 + kNearQueries - 1) / kNearQueries, b2 = (n2 + kNearQueries - 1) / kNearQueries;
     hipLaunchKernelGGL((k_nn_nearest<kNnKey, false>), dim3(b1 + b2), dim3(kGridThreads), 0, st, q12, q21, b1);
     const NnJob ja = nn_job(s1, n1, s2, n2, q12.key), jb = nn_job(s2, n2, s1, n1, q21.key);
@@ -78,6 +113,61 @@ __global__ void k_topk_mean(const int32_t *idx, const float *sh1, uint32_t n1, u
     }
 }
 
+// The K nearest, a wave per query; a query that would walk more than q.walk
+// candidates is left over.
+static __global__ __launch_bounds__(kGridThreads) void k_topk_waves(NnQuery q) {
+    __shared__ NnRestLds s;
+    __shared__ uint32_t s_at[kRestWaves + 1];
+    const uint32_t t = blockIdx.x * (uint32_t)kRestWaves + (threadIdx.x >> 6);
+    const bool left = t < q.nq && !nn_rest_wave<kNnIndex, false>(q, t, s, q.walk);
+    nn_append_left_block(q, left && (threadIdx.x & 63u) == 0, t, s_at);
+}
+
+// The queries left over, a wave each; or, if there are many, all queries by
+// brute force.
+template <int KM>
+static __global__ __launch_bounds__(kGridThreads, 6) void k_topk_rest(NnQuery q, const float *s1, uint32_t n1,
+                                                                   const float *s2, uint32_t n2) {
+    __shared__ NnRestLds s;
+    const uint32_t n = *q.list_n;
+    if (n > q.list_most) {
+        if (blockIdx.x * kTopkQueries >= n2) return;
+        unsigned long long best[KM];
+        topk_brute(s1, n1, s2, n2, q.K, blockIdx.x, best);
+        const uint32_t j = topk_query(blockIdx.x);
+        if (j >= n2 || threadIdx.x % (uint32_t)kTopkLanes != 0) return;
+#pragma unroll
+        for (int k = 0; k < KM; ++k)
+            if (k < q.K) q.idx[(size_t)j * q.K + k] = k < q.keff ? (int32_t)(uint32_t)(best[k] & 0xFFFFFFFFull) : -1;
+        return;
+    }
+    for (uint32_t i = blockIdx.x * (uint32_t)kRestWaves + (threadIdx.x >> 6); i < n; i += gridDim.x * (uint32_t)kRestWaves)
+        nn_rest_wave<kNnIndex, false>(q, q.list[i], s);
+}
+
+static hipError_t topk_search(NnQuery q, const float *s1, uint32_t n1, const float *s2, uint32_t n2, hipStream_t st) {
+    if (q.K > kTopkBruteK) return launch_search<kNnIndex, false>(q, st);
+    q.list_most = n2 / 4u;
+    const uint32_t eighth = n1 / 8u > 256u ? n1 / 8u : 256u;
+    q.walk = q.K == 1 || nn_by_thread(q.K, n2) ? (eighth < kNnMaxWalk ? eighth : kNnMaxWalk) : eighth;
+    const dim3 threads(kGridThreads);
+    if (q.K == 1) {
+        const uint32_t blocks = (n2 + kNearQueries - 1) / kNearQueries;
+        hipLaunchKernelGGL((k_nn_nearest<kNnIndex, false>), dim3(blocks), threads, 0, st, q, q, blocks);
+    } else if (!nn_by_thread(q.K, n2)) {
+        hipLaunchKernelGGL(k_topk_waves, dim3((n2 + kRestWaves - 1) / kRestWaves), threads, 0, st, q);
+    } else {
+        const dim3 blocks((n2 + kGridThreads - 1) / kGridThreads);
+        if (q.K <= 4) hipLaunchKernelGGL((k_nn_query<4, kNnIndex, false>), blocks, threads, 0, st, q);
+        else hipLaunchKernelGGL((k_nn_query<8, kNnIndex, false>), blocks, threads, 0, st, q);
+    }
+    const uint32_t bb = (n2 + kTopkQueries - 1) / kTopkQueries, rb = rest_blocks(n2);
+    const dim3 blocks(bb > rb ? bb : rb);
+    if (q.K <= 4) hipLaunchKernelGGL(k_topk_rest<4>, blocks, threads, 0, st, q, s1, n1, s2, n2);
+    else hipLaunchKernelGGL(k_topk_rest<8>, blocks, threads, 0, st, q, s1, n1, s2, n2);
+    return hipGetLastError();
+}
+
 uint64_t topk_grid_bytes(uint64_t n1, uint64_t n2, int K) {
     auto up = [](uint64_t x) { return (x + 255) & ~255ull; };
     return up(grid_bytes(n1).bytes) + up(grid_bytes(n2).bytes) + up(4 * n2 * (uint64_t)K);
@@ -94,7 +184,7 @@ hipError_t launch_topk_grid(uint32_t n1, const float *s1, const float *sh1, uint
     if (e != hipSuccess) return e;
     NnQuery q = grid_query(b, a, K, n1);
     q.idx = idx ? idx : own;
-    e = launch_search<kNnIndex, false>(q, st);
+    e = topk_search(q, s1, n1, s2, n2, st);
     if (e != hipSuccess) return e;
     const uint64_t values = (uint64_t)n2 * (uint32_t)k3;
     const uint64_t mean_blocks = (values + 255) / 256;

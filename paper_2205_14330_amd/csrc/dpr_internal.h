@@ -419,11 +419,9 @@ hipError_t launch_hull(const HullJob &job, uint8_t *ws, uint64_t *kept_host, hip
 
 // Video warm start: Chamfer distance, top-k SH transfer, Adam (chamfer.hip).
 constexpr int kTopkMax = 32;
-// n1 n2 from which the grid is searched: its seven to nine launches cost about
-// 40 us however small the clouds.  Eq. (9) of 6000 and 8000 points takes 34 and
-// 42 us by brute force (12000: 82, against 43); the 4 nearest 35 us for 500
-// points and 53 for 1000.
-constexpr double kChamferGridPairs = 6.4e7, kTopkGridPairs = 5.0e5;
+// Whether the grid is searched.
+bool chamfer_by_grid(uint64_t n1, uint64_t n2);
+bool topk_by_grid(uint64_t n1, int K);
 struct ChamferLayout {
     uint64_t key12, key21, acc, cnt, part1, part2, bytes;
 };

@@ -36,6 +36,7 @@
 #include <cmath>
 
 #include "dpr_internal.h"
+#include "nn_brute.h"
 
 namespace dpr {
 
@@ -138,12 +139,11 @@ inline NnCloud grid_cloud(const float *xyz, uint64_t n, float density, uint8_t *
     return c;
 }
 
-__device__ __forceinline__ float nn_dist2(float ax, float ay, float az, float bx, float by, float bz) {
-#pragma clang fp contract(off)
-    const float a = ax - bx, b = ay - by, c = az - bz;
-    float s = a * a;
-    s = s + b * b;
-    return s + c * c;
+// LDS written before by any lane of the wave is readable after, and the other way round.
+__device__ __forceinline__ void nn_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Cell of coordinate t (in cells from the grid's origin) on an axis of n cells;
@@ -305,6 +305,7 @@ static __global__ __launch_bounds__(kGridThreads) void k_grid_count(NnCloud a, N
     __shared__ float s_w[6][kGridThreads / 64];
     __shared__ float s_box[6];
     __shared__ uint32_t s_n[kGridThreads / 64];
+    __shared__ uint32_t s_cell[kGridThreads / 64][64];
     __shared__ GridGeom s_g;
     const bool first = blockIdx.x < blocks_a;
     const uint32_t bid = first ? blockIdx.x : blockIdx.x - blocks_a;
@@ -335,11 +336,37 @@ static __global__ __launch_bounds__(kGridThreads) void k_grid_count(NnCloud a, N
 #pragma unroll
     for (int k = 0; k < kGridItems / kGridThreads; ++k) {
         const uint32_t i = bid * (uint32_t)kGridItems + (uint32_t)k * kGridThreads + threadIdx.x;
-        if (i < c.n) {
-            const uint32_t cl = grid_cell(g, p[k][0], p[k][1], p[k][2]);
-            c.cell[i] = cl;
-            c.rank[i] = atomicAdd(c.table + cl, 1u);
+        const uint32_t cl = grid_cell(g, p[k][0], p[k][1], p[k][2]);
+        if (i < c.n) c.cell[i] = cl;
+        const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+        const uint32_t prev = __shfl_up(cl, 1, 64);
+        if (__popcll(__ballot(i < c.n && lane > 0u && prev == cl)) < 2) {
+            if (i < c.n) c.rank[i] = atomicAdd(c.table + cl, 1u);
+            continue;
         }
+        // points in a row share cells (few cells hold most of the cloud, or its points are sorted): groups of the wave's
+        // points in one cell take their places by one atomic each, as a cell's atomics take 10 ns each
+        s_cell[wave][lane] = cl;
+        nn_wave_sync();
+        uint64_t todo = __ballot(i < c.n);
+        uint32_t lead = lane, at = 0, many = 1;
+        for (int round = 0; round < 16 && todo != 0ull; ++round) {
+            const uint32_t l = (uint32_t)__builtin_ctzll(todo);
+            const uint64_t m = __ballot(((todo >> lane) & 1ull) != 0ull && s_cell[wave][l] == cl);
+            const uint32_t in_cell = (uint32_t)__popcll(m);
+            if (in_cell < 5u) break;                      // small groups, one by one
+            if ((m >> lane) & 1ull) {
+                lead = l;
+                at = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                many = in_cell;
+            }
+            todo &= ~m;
+        }
+        nn_wave_sync();
+        if (i < c.n && lead == lane) s_cell[wave][lane] = atomicAdd(c.table + cl, many);
+        nn_wave_sync();
+        if (i < c.n) c.rank[i] = s_cell[wave][lead] + at;
+        nn_wave_sync();
     }
 }
 
@@ -419,6 +446,8 @@ struct NnQuery {
     const uint32_t *table;
     const float4 *pts;
     uint32_t *list, *list_n;    // [nq] queries left for a wave each, their number (cleared before)
+    uint32_t list_most;         // beyond this number only that there are more is kept: the search is done otherwise
+    uint32_t walk;              // candidates beyond which a query is left over
     // outputs, by the query's index
     unsigned long long *key;    // kNnKey: the nearest's (d2 bits << 32 | index), ~0 if none is at a finite distance
     int32_t *idx;               // kNnIndex, kNnIndexDist, kNnSpread: [nq][K], -1 past keff
@@ -429,28 +458,6 @@ struct NnQuery {
     // are pos[] of the points', ascending with them
     const uint32_t *alive, *pos;
 };
-
-template <int KMAX>
-__device__ __forceinline__ void nn_insert(unsigned long long (&best)[KMAX], int K, unsigned long long x,
-                                          unsigned long long &worst) {
-    if (x >= worst) return;
-    // keep the smaller key in each place, carry the larger one on
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-        if (k < K) {
-            const unsigned long long lo = best[k] < x ? best[k] : x;
-            x = best[k] < x ? x : best[k];
-            best[k] = lo;
-        }
-    }
-    if (KMAX == 1) {
-        worst = best[0];
-    } else {
-#pragma unroll
-        for (int k = 0; k < KMAX; ++k)
-            if (k == K - 1) worst = best[k];
-    }
-}
 
 // 0 if delta, the standard deviation of the keff neighbour distances, exceeds
 // eps: float32, each operation rounded, in neighbour order.
@@ -607,11 +614,11 @@ __device__ __forceinline__ void nn_walk_runs(const NnQuery &a, const float4 &q, 
     }
 }
 
-// LDS written before by any lane of the wave is readable after, and the other way round.
-__device__ __forceinline__ void nn_wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// n more queries left over: their first place in the list, or list_most + 1 if
+// it is already longer than list_most (the atomics on one address take 10 ns each).
+__device__ __forceinline__ uint32_t nn_list_place(const NnQuery &a, uint32_t n) {
+    const bool full = a.list_most != 0xFFFFFFFFu && *(const volatile uint32_t *)a.list_n > a.list_most;
+    return full ? a.list_most + 1u : atomicAdd(a.list_n, n);
 }
 
 // The queries t left over, appended to the list wave by wave.
@@ -619,12 +626,34 @@ __device__ __forceinline__ void nn_append_left(const NnQuery &a, bool left, uint
     const uint32_t tid = threadIdx.x;
     const uint64_t rest = __ballot(left);
     if (rest != 0ull) {
-        if ((tid & 63u) == (uint32_t)__builtin_ctzll(rest)) s_at[tid >> 6] = atomicAdd(a.list_n, (uint32_t)__popcll(rest));
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if ((tid & 63u) == (uint32_t)__builtin_ctzll(rest)) s_at[tid >> 6] = nn_list_place(a, (uint32_t)__popcll(rest));
+        nn_wave_sync();
         if (left && a.key) a.key[__float_as_uint(a.q[t].w)] = ~0ull;     // for a search by brute force
-        if (left) a.list[s_at[tid >> 6] + (uint32_t)__popcll(rest & ((1ull << (tid & 63u)) - 1ull))] = t;
+        if (left && s_at[tid >> 6] <= a.list_most)
+            a.list[s_at[tid >> 6] + (uint32_t)__popcll(rest & ((1ull << (tid & 63u)) - 1ull))] = t;
+    }
+}
+
+// The same block by block, where a wave has few queries (s: a word per wave and one).
+__device__ __forceinline__ void nn_append_left_block(const NnQuery &a, bool left, uint32_t t, uint32_t *s) {
+    constexpr uint32_t kWaves = kGridThreads / 64;
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+    const uint64_t rest = __ballot(left);
+    if (lane == 0) s[wave] = (uint32_t)__popcll(rest);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t n = 0;
+        for (uint32_t w = 0; w < kWaves; ++w) n += s[w];
+        if (n) s[kWaves] = nn_list_place(a, n);
+    }
+    __syncthreads();
+    if (left) {
+        if (a.key) a.key[__float_as_uint(a.q[t].w)] = ~0ull;             // for a search by brute force
+        uint32_t at = s[kWaves];
+        if (at <= a.list_most) {
+            for (uint32_t w = 0; w < wave; ++w) at += s[w];
+            a.list[at + (uint32_t)__popcll(rest & ((1ull << lane) - 1ull))] = t;
+        }
     }
 }
 
@@ -654,7 +683,7 @@ template <int KMAX, int MODE, bool SELF>
 static __global__ __launch_bounds__(kGridThreads) void k_nn_query(NnQuery a) {
     __shared__ uint2 s_run[9][kGridThreads];
     __shared__ unsigned long long s_buf[kNnBuf][kGridThreads];
-    __shared__ uint32_t s_at[kGridThreads / 64];
+    __shared__ uint32_t s_at[kGridThreads / 64 + 1];
     const uint32_t t = blockIdx.x * kGridThreads + threadIdx.x, tid = threadIdx.x;
     const bool valid = t < a.nq;
     const GridGeom g = *a.geom;
@@ -699,7 +728,7 @@ static __global__ __launch_bounds__(kGridThreads) void k_nn_query(NnQuery a) {
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) best[k] = ~0ull;
     unsigned long long worst = ~0ull;
-    bool left = valid && total > kNnMaxWalk;
+    bool left = valid && total > a.walk;
     const bool walk = valid && !left;
     nn_walk_runs<KMAX, SELF>(a, q, walk && total > 0 && a.keff > 0, far, s_run, s_buf, best, worst);
     if (walk) {
@@ -733,7 +762,7 @@ constexpr int kNearLanes = 16;
 template <int MODE, bool SELF>
 static __global__ __launch_bounds__(kGridThreads) void k_nn_nearest(NnQuery qa, NnQuery qb, uint32_t blocks_a) {
     __shared__ uint32_t s_beg[kGridThreads], s_pre[kGridThreads], s_end[kGridThreads];
-    __shared__ uint32_t s_at[kGridThreads / 64];
+    __shared__ uint32_t s_at[kGridThreads / 64 + 1];
     const bool first = blockIdx.x < blocks_a;
     const uint32_t bid = first ? blockIdx.x : blockIdx.x - blocks_a;
     const NnQuery &a = first ? qa : qb;
@@ -773,7 +802,7 @@ static __global__ __launch_bounds__(kGridThreads) void k_nn_nearest(NnQuery qa, 
         s_end[tid] = incl;
         nn_wave_sync();
         const uint32_t total = s_end[g0 + kNearLanes - 1u];
-        if (total > kNnMaxWalk) { left = on; on = false; }
+        if (total > a.walk) { left = on; on = false; }
         if (on) {
             for (uint32_t c = l; c < total; c += kNearLanes) {
                 uint32_t lo = g0;                          // the last run that starts at or before c
@@ -805,7 +834,7 @@ static __global__ __launch_bounds__(kGridThreads) void k_nn_nearest(NnQuery qa, 
         unsigned long long b[1] = {best};
         nn_write<1, MODE>(a, self, b);
     }
-    nn_append_left(a, left && l == 0, t, s_at);
+    nn_append_left_block(a, left && l == 0, t, s_at);
 }
 
 constexpr int kRestWaves = kGridThreads / 64;
@@ -822,8 +851,10 @@ struct NnRestLds {
 // holds the k-th smallest key so far.  64 candidates of which one is below the
 // K-th are merged at once: every lane counts the keys below its candidate and
 // below its list entry, which are their places in the merged list.
+// False, with nothing written, as soon as more than `most` candidates are to be
+// walked.
 template <int MODE, bool SELF, bool FILTERED = false>
-__device__ __forceinline__ void nn_rest_wave(const NnQuery &a, uint32_t t, NnRestLds &s) {
+__device__ __forceinline__ bool nn_rest_wave(const NnQuery &a, uint32_t t, NnRestLds &s, uint32_t most = 0xFFFFFFFFu) {
     const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
     const GridGeom g = *a.geom;
     const float4 q = a.q[t];
@@ -835,6 +866,7 @@ __device__ __forceinline__ void nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
     s.list[0][wave][lane] = s.list[1][wave][lane] = ~0ull;
     const float m = nn_margin(g), hs = g.hs;
     int done = -1;                                       // the cube of `done` cells has been walked
+    uint32_t met = 0;                                    // candidates so far (below 2^31)
     bool any = false;                                    // a candidate was met (the same in every lane)
     for (int r = 1;;) {
         const int z0 = max(cz - r, 0), z1 = min(cz + r, (int)g.nz - 1), y0 = max(cy - r, 0), y1 = min(cy + r, (int)g.ny - 1);
@@ -892,6 +924,8 @@ __device__ __forceinline__ void nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
                 s.len[wave][lane] = incl;
                 nn_wave_sync();
                 const uint32_t all = s.len[wave][63];
+                met += all;
+                if (met > most) return false;                // the same in every lane
                 for (uint32_t c0 = 0; c0 < all; c0 += 64u) {
                     const uint32_t c = c0 + lane;
                     unsigned long long x = ~0ull;
@@ -937,7 +971,7 @@ __device__ __forceinline__ void nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
     }
     if (MODE == kNnKey) {
         if (lane == 0) a.key[self] = nn_finite(best);
-        return;
+        return true;
     }
     if (MODE == kNnSpread) {
         s.key[0][wave][lane] = best;
@@ -951,6 +985,7 @@ __device__ __forceinline__ void nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
         a.idx[(size_t)i * a.K + lane] = !ok ? -1 : (int32_t)(FILTERED ? a.pos[j] : j);
         if (MODE == kNnIndexDist) a.d2[(size_t)i * a.K + lane] = ok ? __uint_as_float((uint32_t)(best >> 32)) : 0.f;
     }
+    return true;
 }
 
 // ALL: every query, not only the listed ones.
@@ -966,7 +1001,7 @@ static __global__ __launch_bounds__(kGridThreads) void k_nn_rest(NnQuery qa) {
 // points (idx): where none of those was removed they are the same, numbered by
 // pos.  The other points that are left are listed for a search.
 static __global__ __launch_bounds__(kGridThreads) void k_nn_renumber(NnQuery a, const int32_t *idx) {
-    __shared__ uint32_t s_at[kGridThreads / 64];
+    __shared__ uint32_t s_at[kGridThreads / 64 + 1];
     const uint32_t t = blockIdx.x * kGridThreads + threadIdx.x;
     bool left = false;
     if (t < a.nq) {
@@ -1000,6 +1035,8 @@ static inline NnQuery grid_query(const NnCloud &q, const NnCloud &c, int K, uint
     a.pts = c.pts;
     a.list = q.cell;
     a.list_n = q.cursor + 1;
+    a.list_most = 0xFFFFFFFFu;
+    a.walk = kNnMaxWalk;
     a.key = nullptr;
     a.idx = nullptr;
     a.d2 = nullptr;
