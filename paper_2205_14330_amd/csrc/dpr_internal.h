@@ -412,7 +412,7 @@ struct HullJob {
     int k3;
     bool sync;                   // wait for the kept count
 };
-uint64_t hull_blocks(uint64_t n);
+uint64_t hull_blocks(uint64_t n, bool points = false);     // of n given points, or sampled candidates
 // cams: host table (width, height used)
 HullLayout hull_layout(uint64_t n, int32_t n_cams, const HullCam *cams);
 hipError_t launch_hull(const HullJob &job, uint8_t *ws, uint64_t *kept_host, hipStream_t st);

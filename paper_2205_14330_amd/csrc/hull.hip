@@ -28,17 +28,24 @@ namespace dpr {
 constexpr int kHullThreads = 256;
 constexpr int kHullWaves = kHullThreads / 64;
 constexpr int kHullPer = 8;                                  // items per lane of the compacting form
-constexpr uint64_t kHullMany = 1u << 20;                     // items from which it is taken (below)
+constexpr uint64_t kHullMany = 1u << 20;                     // candidates from which it is taken (below)
+constexpr uint64_t kHullManyPoints = 1u << 22;               // points from which it is taken
 
 // Items per thread of a block: one, or kHullPer from kHullMany items on.  Below,
 // items packed kHullPer to a lane leave too few waves (a whole sampling call
 // with 16 masks of 800x800, one per lane against kHullPer: 2^16 candidates 80
 // us and 107, 2^19 91 and 99, 2^20 110 and 102, 2^22 205 and 154, 2^24 585 and
-// 344).
-__host__ __device__ constexpr int hull_per(uint64_t n) { return n < kHullMany ? 1 : kHullPer; }
+// 344).  Given points are mostly inside (a trained cloud is filtered once per
+// epoch), so packing removes few of them, and they are read, not drawn: the
+// predicate alone, 16 full masks, one per lane against kHullPer, 2^20 points 47
+// us and 74, 2^21 82 and 88, 2^22 155 and 158 (with a fifth inside, 47 and 50,
+// 69 and 60, 124 and 110).
+__host__ __device__ constexpr int hull_per(uint64_t n, bool points) {
+    return n < (points ? kHullManyPoints : kHullMany) ? 1 : kHullPer;
+}
 
-uint64_t hull_blocks(uint64_t n) {
-    const uint64_t items = (uint64_t)kHullThreads * hull_per(n);
+uint64_t hull_blocks(uint64_t n, bool points) {
+    const uint64_t items = (uint64_t)kHullThreads * hull_per(n, points);
     return (n + items - 1) / items;
 }
 
@@ -454,8 +461,9 @@ hipError_t launch_hull(const HullJob &job, uint8_t *ws, uint64_t *kept_host, hip
                        dim3(kHullThreads), 0, st, a.cams, job.n_cams, L.words, packed);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const uint64_t nb = hull_blocks(job.n);
-    const bool many = hull_per(job.n) == kHullPer;
+    const bool points = job.xyz != nullptr;
+    const uint64_t nb = hull_blocks(job.n, points);
+    const bool many = hull_per(job.n, points) == kHullPer;
     if (many)
         hipLaunchKernelGGL(k_hull_flags_many, dim3((uint32_t)nb), dim3(kHullThreads), 0, st, a);
     else
