@@ -34,7 +34,9 @@
  * The library never allocates device memory: the caller provides three
  * workspaces whose sizes the library reports (plan, forward, backward).
  * All float arrays are float32, densely packed, 4-byte aligned; 16-byte
- * alignment of xyz/sh/images is recommended.
+ * alignment of xyz/sh/images is recommended.  Workspaces begin at a multiple of
+ * 16 bytes (of 8 for dpr_knn, dpr_voxel_reduce, dpr_hybrid_update, dpr_chamfer
+ * and the hull's); only dpr_topk_sh_ws checks it.
  *
  * Streams: a stream argument is a hipStream_t passed as void* (NULL = the
  * default stream).  Everything is asynchronous on that stream except

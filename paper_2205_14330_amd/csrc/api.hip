@@ -1213,8 +1213,8 @@ int dpr_chamfer(int64_t n1, const float *s1, int64_t n2, const float *s2, double
     if (!ws || ws_bytes < L.bytes) return fail(DPR_ERR_WORKSPACE, "workspace needs %llu bytes", (unsigned long long)L.bytes);
     if (fault_injected("launch")) return fail(DPR_ERR_HIP, "injected launch failure (DPR_FAULT=launch)");
     // a workspace of the brute-force search's size is enough for that search
-    const bool grid = chamfer_by_grid((uint64_t)n1, (uint64_t)n2) && ws_bytes >= chamfer_grid_bytes((uint64_t)n1, (uint64_t)n2) &&
-                      ((uintptr_t)ws & 15) == 0;
+    const bool grid = chamfer_by_grid((uint64_t)n1, (uint64_t)n2) &&
+                      ws_bytes >= chamfer_grid_bytes((uint64_t)n1, (uint64_t)n2);
     if (grid)
         HIP_TRY(launch_chamfer_grid((uint32_t)n1, s1, (uint32_t)n2, s2, cd, grad2, nn12, nn21,
                                     static_cast<uint8_t *>(ws), static_cast<hipStream_t>(stream)));

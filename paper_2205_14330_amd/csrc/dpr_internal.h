@@ -363,7 +363,7 @@ struct HyScratch {
     uint64_t *part;                               // scan_partials(max(n + 1, hist words)) + 1
     uint64_t *total64;
     uint32_t *flags, *seg, *starts;               // [n + 2] each
-    uint32_t *cell_start;                         // the neighbour grid (grid_bytes of nn_grid.h; 16-byte aligned)
+    uint32_t *cell_start;                         // the neighbour grid (grid_bytes of nn_grid.h)
     float *box_part, *box;                        // [6 kHyBoxBlocks], [6]
     int32_t *idx;                                 // [n K]
     float *d2;                                    // [n K]

@@ -95,7 +95,8 @@ inline float nn_density(int K, uint64_t queries) {
     return fmaxf(1.5f, (nn_by_thread(K, queries) ? 0.4f : 0.2f) * (float)K);
 }
 
-// Byte layout of a cloud's grid inside one buffer (16-byte aligned regions).
+// Byte layout of a cloud's grid inside one buffer: 16-byte aligned regions from
+// the first 16-byte aligned address on (a caller's workspace may begin anywhere).
 struct GridBytes {
     uint64_t part, occ, geom, cursor, table, cell, rank, pts, bytes;
 };
@@ -115,12 +116,13 @@ inline GridBytes grid_bytes(uint64_t n) {
     b.table = add(4 * (uint64_t)grid_max_cells(n));
     b.cell = add(4 * n);
     b.rank = add(4 * n);
-    b.bytes = off;
+    b.bytes = off + 15;
     return b;
 }
 
 inline NnCloud grid_cloud(const float *xyz, uint64_t n, float density, uint8_t *ws) {
     const GridBytes b = grid_bytes(n);
+    ws += (16 - ((uintptr_t)ws & 15)) & 15;
     NnCloud c;
     c.xyz = xyz;
     c.n = (uint32_t)n;
