@@ -184,90 +184,67 @@ hipError_t launch_scan(const uint32_t *in, uint32_t *out, uint64_t n, uint64_t *
 // ---------------------------------------------------------------------------
 // radix sort
 // ---------------------------------------------------------------------------
-struct SortSeg {
-    uint32_t lb;       // block index within the segment
-    uint32_t beg, end; // item range of this block
-    uint32_t nsb;      // sort blocks of the segment
-    uint32_t base;     // first item of the segment
-    uint64_t hist_off;
-};
-
-// One segment of n keys, blocks of kSortTile keys.
-struct FlatSeg {
-    uint32_t n, nblocks;
-    __device__ __forceinline__ SortSeg operator()() const {
-        SortSeg s;
-        s.lb = blockIdx.x;
-        s.base = 0;
-        s.beg = blockIdx.x * (uint32_t)kSortTile;
-        s.end = min(s.beg + (uint32_t)kSortTile, n);
-        s.nsb = nblocks;
-        s.hist_off = 0;
-        return s;
-    }
-};
-
-template <int THREADS, class SEG>
-__global__ __launch_bounds__(THREADS) void k_radix_hist(SEG seg, const uint32_t *keys, uint32_t *hist, int shift) {
+// Blocks of kSortTile keys; hist: [digit][block].
+__global__ __launch_bounds__(kSortThreads) void k_radix_hist(uint32_t n, const uint32_t *keys, uint32_t *hist,
+                                                            int shift) {
     __shared__ uint32_t h[256];
-    const SortSeg sg = seg();
-    for (uint32_t d = threadIdx.x; d < 256u; d += THREADS) h[d] = 0;
+    const uint32_t beg = blockIdx.x * (uint32_t)kSortTile, end = min(beg + (uint32_t)kSortTile, n);
+    for (uint32_t d = threadIdx.x; d < 256u; d += kSortThreads) h[d] = 0;
     __syncthreads();
     // eight keys per thread loaded together, then counted
-    for (uint32_t i0 = sg.beg + threadIdx.x; i0 < sg.end; i0 += 8u * THREADS) {
+    for (uint32_t i0 = beg + threadIdx.x; i0 < end; i0 += 8u * kSortThreads) {
         uint32_t kk[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const uint32_t i = i0 + (uint32_t)u * THREADS;
-            kk[u] = i < sg.end ? keys[i] : 0u;
+            const uint32_t i = i0 + (uint32_t)u * kSortThreads;
+            kk[u] = i < end ? keys[i] : 0u;
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            if (i0 + (uint32_t)u * THREADS < sg.end) atomicAdd(&h[(kk[u] >> shift) & 255u], 1u);
+            if (i0 + (uint32_t)u * kSortThreads < end) atomicAdd(&h[(kk[u] >> shift) & 255u], 1u);
     }
     __syncthreads();
-    for (uint32_t d = threadIdx.x; d < 256u; d += THREADS)
-        hist[sg.hist_off + (uint64_t)d * sg.nsb + sg.lb] = h[d];
+    for (uint32_t d = threadIdx.x; d < 256u; d += kSortThreads)
+        hist[(uint64_t)d * gridDim.x + blockIdx.x] = h[d];
 }
 
-// Stable scatter of one block of THREADS * ITEMS keys by one 8-bit digit.
+// Stable scatter of one block of kSortTile keys by one 8-bit digit.
 // `offs` is the exclusive scan of the histogram ([digit][block]).
-template <int THREADS, int ITEMS, class SEG>
-__global__ __launch_bounds__(THREADS) void k_radix_scatter(SEG seg, const uint32_t *keys_in,
-                                                          const uint32_t *vals_in, uint32_t *keys_out,
-                                                          uint32_t *vals_out, const uint32_t *offs, int shift) {
-    constexpr int TILE = THREADS * ITEMS, WAVES = THREADS / 64;
-    static_assert(THREADS >= 256 && THREADS % 64 == 0, "one thread per digit");
-    __shared__ uint32_t s_keys[TILE];
-    __shared__ uint32_t s_vals[TILE];
+__global__ __launch_bounds__(kSortThreads) void k_radix_scatter(uint32_t n, const uint32_t *keys_in,
+                                                               const uint32_t *vals_in, uint32_t *keys_out,
+                                                               uint32_t *vals_out, const uint32_t *offs, int shift) {
+    constexpr int ITEMS = kSortItemsPerThread, WAVES = kSortThreads / 64;
+    static_assert(kSortThreads == 256, "one thread per digit");
+    __shared__ uint32_t s_keys[kSortTile];
+    __shared__ uint32_t s_vals[kSortTile];
     __shared__ uint32_t s_wcnt[WAVES][256];
     __shared__ uint32_t s_run[256];
     __shared__ uint32_t s_start[256];
     __shared__ uint32_t s_gbase[256];
     __shared__ uint32_t s_wave[WAVES];
 
-    const SortSeg sg = seg();
+    const uint32_t beg = blockIdx.x * (uint32_t)kSortTile, end = min(beg + (uint32_t)kSortTile, n);
     const int lane = __lane_id();
     const int wave = threadIdx.x >> 6;
     const uint64_t lt_mask = (1ull << lane) - 1ull;
     const uint32_t tid = threadIdx.x;
 
-    if (tid < 256u) s_run[tid] = 0;
+    s_run[tid] = 0;
     uint32_t k_[ITEMS], v_[ITEMS], r_[ITEMS];
     // the thread's keys and values, all loads in flight together (the
     // ranking rounds below are separated by barriers, past which the
     // compiler does not move loads)
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
-        const uint32_t idx = sg.beg + (uint32_t)r * THREADS + tid;
-        const bool valid = idx < sg.end;
+        const uint32_t idx = beg + (uint32_t)r * kSortThreads + tid;
+        const bool valid = idx < end;
         k_[r] = valid ? keys_in[idx] : 0u;
         v_[r] = valid ? vals_in[idx] : 0u;
     }
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
-        const uint32_t idx = sg.beg + (uint32_t)r * THREADS + tid;
-        const bool valid = idx < sg.end;
+        const uint32_t idx = beg + (uint32_t)r * kSortThreads + tid;
+        const bool valid = idx < end;
         const uint32_t key = k_[r];
         const uint32_t d = (key >> shift) & 255u;
 #pragma unroll
@@ -284,7 +261,7 @@ __global__ __launch_bounds__(THREADS) void k_radix_scatter(SEG seg, const uint32
         const uint32_t lrank = (uint32_t)__popcll(peers & lt_mask);
         if (valid && lrank == 0) s_wcnt[wave][d] = (uint32_t)__popcll(peers);
         __syncthreads();
-        if (tid < 256u) {   // digit tid: running count + earlier waves of this round
+        {   // digit tid: running count + earlier waves of this round
             uint32_t acc = s_run[tid];
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) {
@@ -300,10 +277,8 @@ __global__ __launch_bounds__(THREADS) void k_radix_scatter(SEG seg, const uint32
     }
     // local start of every digit, and the global base of this block's digit runs
     uint32_t total;
-    const uint32_t cnt = tid < 256u ? s_run[tid] : 0u;
-    const uint32_t start = block_excl_scan_u32(cnt, s_wave, &total);
-    if (tid < 256u) s_start[tid] = start;
-    if (tid < 256u) s_gbase[tid] = offs[sg.hist_off + (uint64_t)tid * sg.nsb + sg.lb];
+    s_start[tid] = block_excl_scan_u32(s_run[tid], s_wave, &total);
+    s_gbase[tid] = offs[(uint64_t)tid * gridDim.x + blockIdx.x];
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
@@ -315,8 +290,7 @@ __global__ __launch_bounds__(THREADS) void k_radix_scatter(SEG seg, const uint32
         }
     }
     __syncthreads();
-    const uint32_t count = sg.end > sg.beg ? sg.end - sg.beg : 0u;
-    for (uint32_t i = tid; i < count; i += THREADS) {
+    for (uint32_t i = tid; i < end - beg; i += kSortThreads) {
         const uint32_t key = s_keys[i];
         const uint32_t d = (key >> shift) & 255u;
         const uint32_t dst = s_gbase[d] + (i - s_start[d]);
@@ -333,15 +307,12 @@ hipError_t launch_radix_sort(uint32_t n, int bits, uint32_t *keys, uint32_t *val
     if (n == 0) return hipSuccess;
     const uint32_t nb = (n + kSortTile - 1) / kSortTile;
     const uint64_t nh = (uint64_t)nb * 256u;
-    const FlatSeg seg{n, nb};
     uint32_t *kin = keys, *vin = vals, *kout = keys_alt, *vout = vals_alt;
     for (int shift = 0; shift < bits; shift += 8) {
-        hipLaunchKernelGGL((k_radix_hist<kSortThreads, FlatSeg>), dim3(nb), dim3(kSortThreads), 0, st, seg, kin, hist,
-                           shift);
+        hipLaunchKernelGGL(k_radix_hist, dim3(nb), dim3(kSortThreads), 0, st, n, kin, hist, shift);
         hipError_t e = launch_scan(hist, hist, nh, part, part + scan_partials(nh), st);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_radix_scatter<kSortThreads, kSortItemsPerThread, FlatSeg>), dim3(nb),
-                           dim3(kSortThreads), 0, st, seg, kin, vin, kout, vout, hist, shift);
+        hipLaunchKernelGGL(k_radix_scatter, dim3(nb), dim3(kSortThreads), 0, st, n, kin, vin, kout, vout, hist, shift);
         uint32_t *t;
         t = kin; kin = kout; kout = t;
         t = vin; vin = vout; vout = t;
