@@ -386,8 +386,12 @@ int dpr_consistency_filter(int64_t n, int32_t sh_degree, const float *xyz, const
  * Squared distances in float32, each operation rounded once:
  * d2(x, y) = ((x0 - y0)^2 + (x1 - y1)^2) + (x2 - y2)^2; a nearest neighbour is
  * the point of smallest d2, ties to the lower index.  dpr_chamfer and
- * dpr_topk_sh_ws search through a grid of cells (brute force for small clouds);
- * dpr_topk_sh, which has no workspace, by brute force: its work grows as n1 * n2.
+ * dpr_topk_sh_ws search through a grid of cells (by brute force small clouds, and
+ * such as crowd into a few cells); dpr_topk_sh, which has no workspace, by brute
+ * force: its work grows as n1 * n2.  Among the k nearest, points at an infinite
+ * distance come after all others and NaN distances last; Eq. (9) takes a point
+ * with no other at a finite distance as one without a nearest: index -1, a NaN
+ * distance, a NaN gradient of its own, and no part in another point's.
  * ------------------------------------------------------------------------- */
 
 /* Bytes of the device workspace of dpr_chamfer (0 on bad sizes). */

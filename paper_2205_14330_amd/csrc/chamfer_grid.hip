@@ -15,16 +15,20 @@
 // into a few cells, or lie apart), the first pass leaves queries over: those
 // that would walk more than an eighth of the points, or more than one thread's
 // or 16 lanes' share.  A second kernel searches on for the ones left over, a
-// wave each; if they are more than a quarter, it searches by brute force for
-// all instead (a wave that ranks a whole cloud costs about three times the
-// brute-force kernel's share of a query).  Such clouds then cost the grid on
-// top of the brute-force search.  45k points, brute force alone against this:
-// one point 1000 times as far as the others, Eq. (9) 876 and 891 us, 4 nearest
-// 1128 and 1274; three tight clusters, each cloud's elsewhere, 1427 and 1403,
-// 866 and 1205 (an eighth is walked before it is left); clouds apart, 2578 and
-// 2545, 766 and 853; every point the same, 2585 and 2535, 666 and 779.  With a
-// wave for every query, however many candidates, the 4 nearest took 3501, 2145,
-// 761 and 3072 us.
+// wave each; if they are too many, it searches by brute force for all instead.
+// The line is where the two cost the same: 45k points, half of them in one
+// cell, and a share of the queries beside these, by brute force 941 us in Eq.
+// (9), by wave 917 with 15% and 1280 with 25%; 4 nearest 1290, 904 with 25%, 1175
+// with 40% and 1560 with 60%; 8 nearest 2300, 1341 with 40% and 1833 with 60%
+// (with a fifth of the points in the cell 940, 894 with 40%; 1280, 1012 with 60%;
+// 2290, 1242 with 60%).  So a quarter; half for up to 4 nearest; three quarters.
+// Such clouds then cost the grid on top of the brute-force search.  45k points,
+// brute force alone against this: one point 1000 times as far as the others, Eq.
+// (9) 876 and 891 us, 4 nearest 1128 and 1274; three tight clusters, each
+// cloud's elsewhere, 1427 and 1403, 866 and 1205 (an eighth is walked before it
+// is left); clouds apart, 2578 and 2545, 766 and 853; every point the same, 2585
+// and 2535, 666 and 779.  With a wave for every query, however many candidates,
+// the 4 nearest took 3501, 2145, 761 and 3072 us.
 #include "nn_brute.h"
 #include "nn_grid.h"
 
@@ -147,7 +151,7 @@ static __global__ __launch_bounds__(kGridThreads, 6) void k_topk_rest(NnQuery q,
 
 static hipError_t topk_search(NnQuery q, const float *s1, uint32_t n1, const float *s2, uint32_t n2, hipStream_t st) {
     if (q.K > kTopkBruteK) return launch_search<kNnIndex, false>(q, st);
-    q.list_most = n2 / 4u;
+    q.list_most = q.K <= 4 ? n2 / 2u : n2 / 4u * 3u;
     const uint32_t eighth = n1 / 8u > 256u ? n1 / 8u : 256u;
     q.walk = q.K == 1 || nn_by_thread(q.K, n2) ? (eighth < kNnMaxWalk ? eighth : kNnMaxWalk) : eighth;
     const dim3 threads(kGridThreads);

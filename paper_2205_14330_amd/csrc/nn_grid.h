@@ -22,14 +22,18 @@
 // of that shell that are closer than the K-th.  Queries that need more (far
 // points), or whose cube holds more than kNnMaxWalk candidates (tight
 // clusters), go to a list, and a second kernel gives each a whole wave and a
-// growing cube.  Neither the order of the
-// points in a cell nor that of the rows changes a result: the keys are
-// distinct and totally ordered.
+// growing cube.  (One nearest: 16 lanes per query; few queries or more than 8
+// nearest: a wave each at once.)  Neither the order of the points in a cell nor
+// that of the rows changes a result: the keys are distinct and totally ordered.
+//
+// A point that is not finite lies in the border cells of its axes and is
+// searched like any other: its distances are infinite or NaN, which sort behind
+// the finite ones, so a query that has too few of these walks the whole grid.
 //
 // The float32 distance ((dx dx + dy dy) + dz dz) rounds each operation once.
 //
 // Bound by the loads' latency and by the lists' upkeep, not by memory: the 8
-// nearest of 255k points take 128 us by thread (51M wave instructions, 50 per
+// nearest of 255k points take 131 us by thread (51M wave instructions, 50 per
 // candidate, of which most keep the list), their 33 MB of input and output 6.
 #pragma once
 
