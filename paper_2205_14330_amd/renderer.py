@@ -129,13 +129,13 @@ class Workspace:
         self.bufs = {}
         self.owner = None
 
-    def get(self, name: str, nbytes: int) -> torch.Tensor:
+    def get(self, name: str, nbytes: int, stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
         nbytes = max(int(nbytes), 1)
         b = self.bufs.get(name)
         if b is None or b.numel() < nbytes:
             size = (int(nbytes * self.headroom) + (1 << 21) - 1) & ~((1 << 21) - 1)
             self.bufs.pop(name, None)
-            b = torch.empty(size, dtype=torch.uint8, device=self.device)
+            b = _scratch(size, self.device, stream)
             self.bufs[name] = b
         return b
 
@@ -187,9 +187,7 @@ class Plan:
             check(_abi.DPR_ERR_INVALID_ARG)
         if workspace is not None:
             workspace.owner = self
-            self.plan_ws = workspace.get("plan", nbytes)
-        else:
-            self.plan_ws = torch.empty(int(nbytes), dtype=torch.uint8, device=dev)
+        self.plan_ws = self._buffer("plan", int(nbytes))
         self._plan = ctypes.c_void_p()
         self.ws = None
         self._rendered = False
@@ -214,6 +212,13 @@ class Plan:
             self.forward()
             self._rendered = True
 
+    def _buffer(self, name: str, nbytes: int) -> torch.Tensor:
+        """A workspace of the plan: from its Workspace, or its own; in either case from the pool of the plan's stream,
+        whose kernels may still use it when the plan, or a grown Workspace, gives it back."""
+        if self.workspace is None:
+            return _scratch(nbytes, self.device, self.stream)
+        return self.workspace.get(name, nbytes, self.stream)
+
     def _check_owner(self):
         if self.workspace is not None and self.workspace.owner is not self:
             raise RuntimeError("this plan's Workspace has been handed to a newer plan")
@@ -226,10 +231,7 @@ class Plan:
             return self.images, self.trans
         n = int(self.lib.dpr_workspace_bytes(self._plan))
         if self.ws is None or self.ws.numel() < n:
-            if self.workspace is not None:
-                self.ws = self.workspace.get("fwd", n)
-            else:
-                self.ws = torch.empty(max(n, 1), dtype=torch.uint8, device=self.device)
+            self.ws = self._buffer("fwd", max(n, 1))
         check(self.lib.dpr_render_forward(self._plan, self.ws.data_ptr(), int(self.ws.numel()),
                                           _stream_handle(self.stream)))
         return self.images, self.trans
@@ -261,10 +263,7 @@ class Plan:
                             torch.empty_like(s.sh) if "sh" in want else None,
                             torch.empty_like(s.opacity) if "opacity" in want else None))
         nb = int(self.lib.dpr_backward_ws_bytes(self._plan))
-        if self.workspace is not None:
-            bws = self.workspace.get("bwd", nb)
-        else:
-            bws = torch.empty(max(nb, 1), dtype=torch.uint8, device=self.device)
+        bws = self._buffer("bwd", max(nb, 1))
         P = _abi.ptr_array
         di = P([g.data_ptr() for g in gi])
         dt = None if gt is None else P([0 if g is None else g.data_ptr() for g in gt])
@@ -381,7 +380,7 @@ def loss_l2_tv(renders: Sequence[torch.Tensor], targets: Sequence[torch.Tensor],
     nb = int(lib.dpr_loss_ws_bytes(n, W, H))
     if nb == 0:
         check(_abi.DPR_ERR_INVALID_ARG)
-    ws = workspace.get("loss", nb) if workspace is not None else _scratch(nb, dev, stream)
+    ws = workspace.get("loss", nb, stream) if workspace is not None else _scratch(nb, dev, stream)
     loss = torch.empty(n, dtype=torch.float64, device=dev)
     P = _abi.ptr_array
     check(lib.dpr_loss_l2_tv(n, P([r.data_ptr() for r in renders]), P([t.data_ptr() for t in targets]), W, H,

@@ -1,4 +1,4 @@
-"""Scratch memory of a call on a given stream comes from that stream's pool: it
+"""Scratch memory of a call or a plan on a given stream comes from that stream's pool: it
 is dropped when the call returns, while its kernels still run, and memory of
 another stream's pool could be handed to that stream's next tensor.  Checked on
 the CPU with a stand-in for the library and for the stream context."""
@@ -53,11 +53,25 @@ CALLS = {
     "hull_sample": lambda s: hull.hull_sample(*_views(), (0, 0, 0), (1, 1, 1), 1, 9, stream=s),
     "consistency": lambda s: hull.consistency(_dev(9, 3), *_views(), stream=s),
     "consistency_filter": lambda s: hull.consistency_filter(_scene(), *_views(), stream=s),
+    "loss_l2_tv with a Workspace": lambda s: renderer.loss_l2_tv([_dev(6, 8, 3)], [_dev(6, 8, 3)], stream=s,
+                                                                 workspace=renderer.Workspace("cpu")),
     "loss_l2_tv": lambda s: renderer.loss_l2_tv([_dev(6, 8, 3)], [_dev(6, 8, 3)], stream=s),
 }
 
 
-@pytest.mark.parametrize("name", sorted(CALLS))
+def _plan(workspace):
+    def call(s):
+        cam = workloads.orbit_camera(0, 8, 8, 6)
+        p = renderer.Plan([_scene()], [(0, cam)], stream=s, workspace=workspace() if workspace else None)
+        p.forward()
+        p.backward([_dev(6, 8, 3)])
+    return call
+
+
+PLANS = {"plan": _plan(None), "plan with a Workspace": _plan(lambda: renderer.Workspace("cpu"))}
+
+
+@pytest.mark.parametrize("name", sorted(CALLS) + sorted(PLANS))
 def test_scratch_is_allocated_on_the_calls_stream(monkeypatch, name):
     current, scratch = [None], []
     empty = torch.empty
@@ -69,7 +83,7 @@ def test_scratch_is_allocated_on_the_calls_stream(monkeypatch, name):
         current.pop()
 
     def recorded(*a, **k):
-        if k.get("dtype") == torch.uint8 and a == (1024,):
+        if k.get("dtype") == torch.uint8 and a in ((1024,), (1 << 21,)):
             scratch.append(current[-1])
         return empty(*a, **k)
 
@@ -78,5 +92,5 @@ def test_scratch_is_allocated_on_the_calls_stream(monkeypatch, name):
     monkeypatch.setattr(torch.cuda, "stream", stream)
     monkeypatch.setattr(torch, "empty", recorded)
     side = _Stream()
-    CALLS[name](side)
-    assert scratch == [side]
+    (CALLS.get(name) or PLANS[name])(side)
+    assert scratch == [side] * (3 if name in PLANS else 1)
