@@ -44,17 +44,21 @@ bool chamfer_by_grid(uint64_t n1, uint64_t n2) {
     return (n1 < n2 ? n1 : n2) >= 2000 && (double)n1 * (double)n2 >= 6.4e7;
 }
 // The k nearest by brute force take a time by n1 and K (lanes walk n1 / 8
-// points each), up to some 45k queries.  10k queries, brute force against grid,
-// and on crowded points: K = 4, n1 = 1000 52 and 48 us (47 and 91), 1500 66 and
-// 48, 3000 105 and 48; K = 8, n1 = 300 52 and 51 (51 and 72), 600 69 and 51;
-// K = 16, n1 = 150 83 and 53, 300 104 and 54 (99 and 72).
-bool topk_by_grid(uint64_t n1, int K) { return n1 >= (K <= 4 ? 1500u : K <= 8 ? 600u : 300u); }
+// points each), up to some 45k queries.  2000 queries, brute force against grid:
+// K = 4, n1 = 600 35 and 38 us, 1000 46 and 39, 3000 97 and 39; K = 8, n1 = 300
+// 44 and 40, 600 62 and 38; K = 16, n1 = 150 69 and 39, 300 87 and 39.
+bool topk_by_grid(uint64_t n1, int K) { return n1 >= (K <= 4 ? 1000u : K <= 8 ? 600u : 300u); }
 
 // The most neighbours for which many left over are searched by brute force: a
 // wave's list costs the same for any K, the brute force's insertions grow with
 // it (45k points in three clusters: K = 12 2.7 ms by brute force, 2.8 by wave;
 // with a far point 4.6 and 3.8).
 constexpr int kTopkBruteK = 8;
+// And the fewest queries: the waves of fewer all run at once, while the brute
+// force takes its time whatever their number (45k points, 300 queries, clouds
+// apart: 98 us by wave, 656 by brute force; 9000 x 9000 in two blobs, K = 8, 272
+// and 432; 45k x 45k in three clusters, K = 4, 2145 and 866, K = 8, 2527 and 1377).
+inline uint32_t topk_brute_queries(int K) { return K <= 4 ? 8192u : 32768u; }
 
 // Registers for six waves per SIMD: the blocks of 45k queries by brute force then run all at once.
 __global__ __launch_bounds__(kGridThreads, 6) void k_chamfer_rest(NnQuery qa, NnQuery qb, NnJob ja, NnJob jb) {
@@ -123,8 +127,8 @@ static __global__ __launch_bounds__(kGridThreads) void k_topk_waves(NnQuery q) {
     __shared__ NnRestLds s;
     __shared__ uint32_t s_at[kRestWaves + 1];
     const uint32_t t = blockIdx.x * (uint32_t)kRestWaves + (threadIdx.x >> 6);
-    const bool left = t < q.nq && !nn_rest_wave<kNnIndex, false>(q, t, s, q.walk);
-    nn_append_left_block(q, left && (threadIdx.x & 63u) == 0, t, s_at);
+    const bool left = t < q.nq && !nn_rest_wave<kNnIndex, false, false, true>(q, t, s);
+    nn_append_left_block<true>(q, left && (threadIdx.x & 63u) == 0, t, s_at);
 }
 
 // The queries left over, a wave each; or, if there are many, all queries by
@@ -150,7 +154,7 @@ static __global__ __launch_bounds__(kGridThreads, 6) void k_topk_rest(NnQuery q,
 }
 
 static hipError_t topk_search(NnQuery q, const float *s1, uint32_t n1, const float *s2, uint32_t n2, hipStream_t st) {
-    if (q.K > kTopkBruteK) return launch_search<kNnIndex, false>(q, st);
+    if (q.K > kTopkBruteK || n2 < topk_brute_queries(q.K)) return launch_search<kNnIndex, false>(q, st);
     q.list_most = q.K <= 4 ? n2 / 2u : n2 / 4u * 3u;
     const uint32_t eighth = n1 / 8u > 256u ? n1 / 8u : 256u;
     q.walk = q.K == 1 || nn_by_thread(q.K, n2) ? (eighth < kNnMaxWalk ? eighth : kNnMaxWalk) : eighth;

@@ -49,6 +49,9 @@ constexpr int kGridItems = 4 * kGridThreads;            // points per counting b
 constexpr uint32_t kGridBoxBlocks = 128;                // blocks of the box reduction, per cloud
 constexpr uint32_t kOccAxis = 32;                       // coarse cells per axis, at most
 constexpr uint32_t kOccWords = kOccAxis * kOccAxis * kOccAxis / 32;
+// Points per occupied coarse cell (some 17 in a filled box, 600 of 10M points)
+// above which the cloud crowds into few cells.
+constexpr uint32_t kCrowd = 640;
 constexpr uint32_t kNnMaxWalk = 1024;                   // candidates a single thread walks
 
 struct GridGeom {
@@ -311,8 +314,10 @@ static __global__ __launch_bounds__(kGridThreads) void k_grid_count(NnCloud a, N
     __shared__ float s_w[6][kGridThreads / 64];
     __shared__ float s_box[6];
     __shared__ uint32_t s_n[kGridThreads / 64];
+    constexpr int kPer = kGridItems / kGridThreads;
     __shared__ uint32_t s_cell[kGridThreads / 64][64];
     __shared__ GridGeom s_g;
+    __shared__ bool s_crowd;
     const bool first = blockIdx.x < blocks_a;
     const uint32_t bid = first ? blockIdx.x : blockIdx.x - blocks_a;
     const NnCloud &c = first ? a : b;
@@ -335,23 +340,29 @@ static __global__ __launch_bounds__(kGridThreads) void k_grid_count(NnCloud a, N
         uint32_t t = 0;
         for (int w = 0; w < kGridThreads / 64; ++w) t += s_n[w];
         s_g = grid_geometry(c, s_box, t);
+        s_crowd = c.n / kCrowd > t;
         if (bid == 0) *c.geom = s_g;
     }
     __syncthreads();
     const GridGeom g = s_g;
+    if (!s_crowd) {
 #pragma unroll
-    for (int k = 0; k < kGridItems / kGridThreads; ++k) {
+        for (int k = 0; k < kPer; ++k) {
+            const uint32_t i = bid * (uint32_t)kGridItems + (uint32_t)k * kGridThreads + threadIdx.x;
+            if (i < c.n) {
+                const uint32_t cl = grid_cell(g, p[k][0], p[k][1], p[k][2]);
+                c.cell[i] = cl;
+                c.rank[i] = atomicAdd(c.table + cl, 1u);
+            }
+        }
+        return;
+    }
+    // groups of the wave's points in one cell take their places by one atomic each, as a cell's atomics take 10 ns each
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+#pragma unroll 1
+    for (int k = 0; k < kPer; ++k) {
         const uint32_t i = bid * (uint32_t)kGridItems + (uint32_t)k * kGridThreads + threadIdx.x;
         const uint32_t cl = grid_cell(g, p[k][0], p[k][1], p[k][2]);
-        if (i < c.n) c.cell[i] = cl;
-        const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-        const uint32_t prev = __shfl_up(cl, 1, 64);
-        if (__popcll(__ballot(i < c.n && lane > 0u && prev == cl)) < 2) {
-            if (i < c.n) c.rank[i] = atomicAdd(c.table + cl, 1u);
-            continue;
-        }
-        // points in a row share cells (few cells hold most of the cloud, or its points are sorted): groups of the wave's
-        // points in one cell take their places by one atomic each, as a cell's atomics take 10 ns each
         s_cell[wave][lane] = cl;
         nn_wave_sync();
         uint64_t todo = __ballot(i < c.n);
@@ -371,7 +382,10 @@ static __global__ __launch_bounds__(kGridThreads) void k_grid_count(NnCloud a, N
         nn_wave_sync();
         if (i < c.n && lead == lane) s_cell[wave][lane] = atomicAdd(c.table + cl, many);
         nn_wave_sync();
-        if (i < c.n) c.rank[i] = s_cell[wave][lead] + at;
+        if (i < c.n) {
+            c.cell[i] = cl;
+            c.rank[i] = s_cell[wave][lead] + at;
+        }
         nn_wave_sync();
     }
 }
@@ -452,7 +466,7 @@ struct NnQuery {
     const uint32_t *table;
     const float4 *pts;
     uint32_t *list, *list_n;    // [nq] queries left for a wave each, their number (cleared before)
-    uint32_t list_most;         // beyond this number only that there are more is kept: the search is done otherwise
+    uint32_t list_most;         // if there are more, the list is not read: the search is done otherwise
     uint32_t walk;              // candidates beyond which a query is left over
     // outputs, by the query's index
     unsigned long long *key;    // kNnKey: the nearest's (d2 bits << 32 | index), ~0 if none is at a finite distance
@@ -518,21 +532,21 @@ __device__ __forceinline__ float nn_margin(const GridGeom &g) {
 // (cx, cy, cz) can be: the nearest face that has cells behind it, in cells from
 // the query at (tx, ty, tz), less margins for the rounding of the cell
 // coordinates and of the distances.  Infinite if, and only if, the cube holds
-// the whole grid: of a face at no finite distance (the query is not finite, or
-// far beyond the grid) nothing is said that a K-th distance could be below, as
-// all distances of such a query are infinite or NaN.
+// the whole grid: a face at no finite distance (the query is not finite, or far
+// beyond the grid, so that its distances are infinite or NaN) bounds nothing.
 __device__ __forceinline__ float nn_bound(const GridGeom &g, float tx, float ty, float tz, int cx, int cy, int cz, int r) {
     constexpr float kMost = 3.4028235e38f;               // the largest finite value
-    float f = INFINITY;
-    if (cx - r > 0) f = fminf(fminf(f, tx - (float)(cx - r)), kMost);
-    if (cy - r > 0) f = fminf(fminf(f, ty - (float)(cy - r)), kMost);
-    if (cz - r > 0) f = fminf(fminf(f, tz - (float)(cz - r)), kMost);
-    if (cx + r + 1 < (int)g.nx) f = fminf(fminf(f, (float)(cx + r + 1) - tx), kMost);
-    if (cy + r + 1 < (int)g.ny) f = fminf(fminf(f, (float)(cy + r + 1) - ty), kMost);
-    if (cz + r + 1 < (int)g.nz) f = fminf(fminf(f, (float)(cz + r + 1) - tz), kMost);
-    if (f == INFINITY) return INFINITY;
+    const bool xl = cx - r > 0, yl = cy - r > 0, zl = cz - r > 0;
+    const bool xh = cx + r + 1 < (int)g.nx, yh = cy + r + 1 < (int)g.ny, zh = cz + r + 1 < (int)g.nz;
+    float f = kMost;
+    f = xl ? fminf(f, tx - (float)(cx - r)) : f;
+    f = yl ? fminf(f, ty - (float)(cy - r)) : f;
+    f = zl ? fminf(f, tz - (float)(cz - r)) : f;
+    f = xh ? fminf(f, (float)(cx + r + 1) - tx) : f;
+    f = yh ? fminf(f, (float)(cy + r + 1) - ty) : f;
+    f = zh ? fminf(f, (float)(cz + r + 1) - tz) : f;
     f = fmaxf(f - nn_margin(g), 0.f) * g.hs;
-    return fminf(f * f, kMost);
+    return xl || yl || zl || xh || yh || zh ? fminf(f * f, kMost) : INFINITY;
 }
 
 // Four candidates from i on, the last of the run repeated past its end.
@@ -620,27 +634,23 @@ __device__ __forceinline__ void nn_walk_runs(const NnQuery &a, const float4 &q, 
     }
 }
 
-// n more queries left over: their first place in the list, or list_most + 1 if
-// it is already longer than list_most (the atomics on one address take 10 ns each).
-__device__ __forceinline__ uint32_t nn_list_place(const NnQuery &a, uint32_t n) {
-    const bool full = a.list_most != 0xFFFFFFFFu && *(const volatile uint32_t *)a.list_n > a.list_most;
-    return full ? a.list_most + 1u : atomicAdd(a.list_n, n);
-}
-
 // The queries t left over, appended to the list wave by wave.
 __device__ __forceinline__ void nn_append_left(const NnQuery &a, bool left, uint32_t t, uint32_t *s_at) {
     const uint32_t tid = threadIdx.x;
     const uint64_t rest = __ballot(left);
     if (rest != 0ull) {
-        if ((tid & 63u) == (uint32_t)__builtin_ctzll(rest)) s_at[tid >> 6] = nn_list_place(a, (uint32_t)__popcll(rest));
+        if ((tid & 63u) == (uint32_t)__builtin_ctzll(rest)) s_at[tid >> 6] = atomicAdd(a.list_n, (uint32_t)__popcll(rest));
         nn_wave_sync();
         if (left && a.key) a.key[__float_as_uint(a.q[t].w)] = ~0ull;     // for a search by brute force
-        if (left && s_at[tid >> 6] <= a.list_most)
-            a.list[s_at[tid >> 6] + (uint32_t)__popcll(rest & ((1ull << (tid & 63u)) - 1ull))] = t;
+        if (left) a.list[s_at[tid >> 6] + (uint32_t)__popcll(rest & ((1ull << (tid & 63u)) - 1ull))] = t;
     }
 }
 
-// The same block by block, where a wave has few queries (s: a word per wave and one).
+// The same block by block, where a wave has few queries (s: a word per wave and
+// one): the atomics on one address take 10 ns each.  CHECK: none once the list
+// is longer than it is read; the look at its length is a round trip to memory
+// more, so only where few blocks leave queries over or nearly all do.
+template <bool CHECK>
 __device__ __forceinline__ void nn_append_left_block(const NnQuery &a, bool left, uint32_t t, uint32_t *s) {
     constexpr uint32_t kWaves = kGridThreads / 64;
     const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
@@ -650,13 +660,16 @@ __device__ __forceinline__ void nn_append_left_block(const NnQuery &a, bool left
     if (threadIdx.x == 0) {
         uint32_t n = 0;
         for (uint32_t w = 0; w < kWaves; ++w) n += s[w];
-        if (n) s[kWaves] = nn_list_place(a, n);
+        if (n) {
+            const bool full = CHECK && *(const volatile uint32_t *)a.list_n > a.list_most;
+            s[kWaves] = full ? 0xFFFFFFFFu : atomicAdd(a.list_n, n);
+        }
     }
     __syncthreads();
     if (left) {
         if (a.key) a.key[__float_as_uint(a.q[t].w)] = ~0ull;             // for a search by brute force
         uint32_t at = s[kWaves];
-        if (at <= a.list_most) {
+        if (!CHECK || at != 0xFFFFFFFFu) {
             for (uint32_t w = 0; w < wave; ++w) at += s[w];
             a.list[at + (uint32_t)__popcll(rest & ((1ull << lane) - 1ull))] = t;
         }
@@ -840,7 +853,7 @@ static __global__ __launch_bounds__(kGridThreads) void k_nn_nearest(NnQuery qa, 
         unsigned long long b[1] = {best};
         nn_write<1, MODE>(a, self, b);
     }
-    nn_append_left_block(a, left && l == 0, t, s_at);
+    nn_append_left_block<false>(a, left && l == 0, t, s_at);
 }
 
 constexpr int kRestWaves = kGridThreads / 64;
@@ -857,10 +870,10 @@ struct NnRestLds {
 // holds the k-th smallest key so far.  64 candidates of which one is below the
 // K-th are merged at once: every lane counts the keys below its candidate and
 // below its list entry, which are their places in the merged list.
-// False, with nothing written, as soon as more than `most` candidates are to be
-// walked.
-template <int MODE, bool SELF, bool FILTERED = false>
-__device__ __forceinline__ bool nn_rest_wave(const NnQuery &a, uint32_t t, NnRestLds &s, uint32_t most = 0xFFFFFFFFu) {
+// LIMIT: false, with nothing written, if more than a.walk candidates would have
+// to be walked (it stops at the run that brings them).
+template <int MODE, bool SELF, bool FILTERED = false, bool LIMIT = false>
+__device__ __forceinline__ bool nn_rest_wave(const NnQuery &a, uint32_t t, NnRestLds &s) {
     const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
     const GridGeom g = *a.geom;
     const float4 q = a.q[t];
@@ -929,9 +942,11 @@ __device__ __forceinline__ bool nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
                 s.pre[wave][lane] = incl - (e - b);
                 s.len[wave][lane] = incl;
                 nn_wave_sync();
-                const uint32_t all = s.len[wave][63];
-                met += all;
-                if (met > most) return false;                // the same in every lane
+                uint32_t all = s.len[wave][63];
+                if (LIMIT) {                                 // the same in every lane
+                    met = min(met + all, a.walk + 1u);
+                    all = met > a.walk ? 0u : all;
+                }
                 for (uint32_t c0 = 0; c0 < all; c0 += 64u) {
                     const uint32_t c = c0 + lane;
                     unsigned long long x = ~0ull;
@@ -971,6 +986,7 @@ __device__ __forceinline__ bool nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
         }
         const float kth = __uint_as_float((uint32_t)(worst >> 32));
         const float bound = nn_bound(g, tx, ty, tz, cx, cy, cz, r);
+        if (LIMIT && met > a.walk) return false;
         if (bound == INFINITY || kth < bound) break;     // the same in every lane
         done = r;
         r += any ? (r + 1) / 2 : r;

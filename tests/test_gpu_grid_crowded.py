@@ -24,8 +24,9 @@ def _check(s1, s2, K):
 
 
 @pytest.mark.parametrize("K", [1, 3, 8, 9])
-@pytest.mark.parametrize("n2,share", [(1100, 0.0), (1100, 0.2), (1100, 0.49), (1100, 0.51), (1100, 0.74), (1100, 0.76),
-                                      (1100, 1.0), (65600, 0.2), (65600, 0.6), (65600, 0.9)])
+@pytest.mark.parametrize("n2,share", [(1100, 0.2), (1100, 1.0), (8191, 1.0), (8192, 0.0), (8192, 0.49), (8192, 0.51),
+                                      (8203, 1.0), (32767, 0.9), (32768, 0.74), (32768, 0.76), (65600, 0.2), (65600, 0.6),
+                                      (65600, 0.9)])
 def test_share_of_the_queries_in_a_crowd(n2, share, K):
     """Half of the points in one cell, and `share` of the queries beside them."""
     rng = np.random.default_rng(K)
@@ -37,7 +38,7 @@ def test_share_of_the_queries_in_a_crowd(n2, share, K):
     _check(a, b, K)
 
 
-@pytest.mark.parametrize("n1,K", [(1499, 4), (1500, 4), (1500, 1), (599, 5), (600, 5), (299, 9), (300, 9), (300, 32)])
+@pytest.mark.parametrize("n1,K", [(999, 4), (1000, 4), (1000, 1), (599, 5), (600, 5), (299, 9), (300, 9), (300, 32)])
 def test_sizes_from_which_the_grid_is_searched(n1, K):
     a, b = clouds("surface", 5)
     _check(a[:n1], b[:777], K)
