@@ -22,13 +22,13 @@
 // with 40% and 1560 with 60%; 8 nearest 2300, 1341 with 40% and 1833 with 60%
 // (with a fifth of the points in the cell 940, 894 with 40%; 1280, 1012 with 60%;
 // 2290, 1242 with 60%).  So a quarter; half for up to 4 nearest; three quarters.
-// Such clouds then cost the grid on top of the brute-force search.  45k points,
-// brute force alone against this: one point 1000 times as far as the others, Eq.
-// (9) 876 and 891 us, 4 nearest 1128 and 1274; three tight clusters, each
-// cloud's elsewhere, 1427 and 1403, 866 and 1205 (an eighth is walked before it
-// is left); clouds apart, 2578 and 2545, 766 and 853; every point the same, 2585
-// and 2535, 666 and 779.  With a wave for every query, however many candidates,
-// the 4 nearest took 3501, 2145, 761 and 3072 us.
+// Such clouds then cost the grid and its first pass on top of the brute-force
+// search.  45k points, brute force alone against this: one point 1000 times as
+// far as the others, Eq. (9) 879 and 876 us, 4 nearest 1128 and 1338; three tight
+// clusters, each cloud's elsewhere, 1425 and 1407, 865 and 1379 (an eighth is
+// walked before it is left); clouds apart, 2564 and 2559, 765 and 776; every
+// point the same, 2568 and 2561, 663 and 885.  With a wave for every query,
+// however many candidates, the 4 nearest took 3501, 2145, 761 and 3072 us.
 #include "nn_brute.h"
 #include "nn_grid.h"
 
@@ -45,9 +45,12 @@ bool chamfer_by_grid(uint64_t n1, uint64_t n2) {
 }
 // The k nearest by brute force take a time by n1 and K (lanes walk n1 / 8
 // points each), up to some 45k queries.  2000 queries, brute force against grid:
-// K = 4, n1 = 600 35 and 38 us, 1000 46 and 39, 3000 97 and 39; K = 8, n1 = 300
+// K = 1, n1 = 1000 37 and 35 us, 1500 48 and 36; K = 4, n1 = 600 35 and 38, 1000
+// 46 and 39, 3000 97 and 39; K = 8, n1 = 300
 // 44 and 40, 600 62 and 38; K = 16, n1 = 150 69 and 39, 300 87 and 39.
-bool topk_by_grid(uint64_t n1, int K) { return n1 >= (K <= 4 ? 1000u : K <= 8 ? 600u : 300u); }
+bool topk_by_grid(uint64_t n1, int K) {
+    return n1 >= (K == 1 ? 1500u : K <= 4 ? 1000u : K <= 8 ? 600u : 300u);
+}
 
 // The most neighbours for which many left over are searched by brute force: a
 // wave's list costs the same for any K, the brute force's insertions grow with

@@ -891,7 +891,7 @@ __device__ __forceinline__ bool nn_rest_wave(const NnQuery &a, uint32_t t, NnRes
         const int z0 = max(cz - r, 0), z1 = min(cz + r, (int)g.nz - 1), y0 = max(cy - r, 0), y1 = min(cy + r, (int)g.ny - 1);
         const int xa = max(cx - r, 0), xb = min(cx + r, (int)g.nx - 1);
         const uint32_t ny = (uint32_t)(y1 - y0 + 1), runs = 2u * ny * (uint32_t)(z1 - z0 + 1);
-        for (uint32_t k0 = 0; k0 < runs; k0 += 64u * kRestRuns) {
+        for (uint32_t k0 = 0; k0 < runs && !(LIMIT && met > a.walk); k0 += 64u * kRestRuns) {
             // run k: row k / 2; a row inside the walked cube has a part on either side of it.  The ends of
             // kRestRuns runs per lane are loaded together: most of a large shell is empty.
             uint32_t rb[kRestRuns], re[kRestRuns];

@@ -38,7 +38,7 @@ def test_share_of_the_queries_in_a_crowd(n2, share, K):
     _check(a, b, K)
 
 
-@pytest.mark.parametrize("n1,K", [(999, 4), (1000, 4), (1000, 1), (599, 5), (600, 5), (299, 9), (300, 9), (300, 32)])
+@pytest.mark.parametrize("n1,K", [(999, 4), (1000, 4), (1499, 1), (1500, 1), (599, 5), (600, 5), (299, 9), (300, 9), (300, 32)])
 def test_sizes_from_which_the_grid_is_searched(n1, K):
     a, b = clouds("surface", 5)
     _check(a[:n1], b[:777], K)
