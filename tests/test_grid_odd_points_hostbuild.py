@@ -39,8 +39,9 @@ def test_knn(hybrid, tmp_path, name, K):
     assert same_values(_read(tmp_path, "d2.bin", np.float32, (-1, K)), d2)
 
 
-@pytest.mark.parametrize("odd", ["queries", "points", "both"])
-@pytest.mark.parametrize("name,K", [(n, 1 + 3 * (i % 2)) for i, n in enumerate(NAMES)] + [("nan", 4), ("far", 4)])
+@pytest.mark.parametrize("name,K,odd", [(n, 1 + 3 * (i % 2), ("queries", "both")[i % 2]) for i, n in enumerate(NAMES)] +
+                         [("nan", 4, "queries"), ("nan", 1, "points"), ("far", 4, "queries"), ("far", 1, "points"),
+                          ("inf", 4, "queries"), ("inf", 1, "points"), ("nan coordinate", 4, "points")])
 def test_topk(grid, tmp_path, name, K, odd):
     a = clouds("ball")[0][:200] if odd == "queries" else odd_cloud(name, 200)
     b = clouds("ball")[1][:12] if odd == "points" else odd_cloud(name, 12, 1)
@@ -51,8 +52,8 @@ def test_topk(grid, tmp_path, name, K, odd):
     assert np.array_equal(_read(tmp_path, "out_sh.bin", np.float32, (-1, 4, 3)), mean_rows(sh, idx))
 
 
-@pytest.mark.parametrize("odd", ["s1", "s2", "both"])
-@pytest.mark.parametrize("name", NAMES)
+@pytest.mark.parametrize("name,odd", [(n, ("s1", "s2", "both")[i % 3]) for i, n in enumerate(NAMES)] +
+                         [("nan coordinate", "s1"), ("inf", "s1"), ("inf", "s2"), ("far", "both"), ("nan", "s2")])
 def test_chamfer(grid, brute, tmp_path, name, odd):
     """Through the grid and by brute force: a point at no finite distance of any other has no nearest (-1); it takes
     part in no other point's gradient."""
